@@ -534,92 +534,6 @@ __global__ __launch_bounds__(256) void tail_reduce_kernel(const float* __restric
   }
 }
 
-// ----------------------------------------------------------------------------- fp32 GEMM
-// Plain LDS-tiled fp32 FMA kernel for the fp32 layer: 64 x 64 outputs per
-// block (GEMM-1: 64 features of both gate and up), 4 x 4 per thread.
-constexpr int kFM = 64, kFN = 64, kFK = 16;
-
-struct GemmArgsF {
-  const float* act;
-  const int32_t* gather;          // [R] token of each grouped row, or null
-  const float* w0;
-  const float* w1;
-  float* out;
-  const int32_t* offsets;
-  const int32_t* mtile_prefix;
-  int E, K, N, ntiles;
-};
-
-template <bool SWIGLU>
-__global__ __launch_bounds__(256) void grouped_gemm_f32_kernel(GemmArgsF p) {
-  __shared__ float sX[kFK][kFM + 4];
-  __shared__ float sG[kFK][kFN + 4];
-  __shared__ float sU[kFK][kFN + 4];
-  __shared__ int32_t s_pref[kMaxExperts + 1];
-  const int tid = threadIdx.x;
-  for (int i = tid; i <= p.E; i += 256) s_pref[i] = p.mtile_prefix[i];
-  __syncthreads();
-  const int64_t L = blockIdx.x;
-  if (L >= int64_t(s_pref[p.E]) * p.ntiles) return;           // uniform across the block
-  const int e = find_expert(s_pref, p.E, L / p.ntiles);
-  const int64_t local = L - int64_t(s_pref[e]) * p.ntiles;
-  const int mt = int(local / p.ntiles), nt = int(local % p.ntiles);
-  const int row0 = p.offsets[e] + mt * kFM;
-  const int row_end = p.offsets[e + 1];
-  const int n0 = nt * kFN;
-  const int K = p.K, N = p.N;
-  const float* wg = p.w0 + int64_t(e) * N * K;
-  const float* wu = SWIGLU ? p.w1 + int64_t(e) * N * K : nullptr;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;               // loader: one float4 per thread
-  const int64_t arow = p.gather != nullptr ? int64_t(p.gather[min(row0 + lrow, row_end - 1)])
-                                           : int64_t(min(row0 + lrow, row_end - 1));
-  const int64_t wrow = min(n0 + lrow, N - 1);
-  float ag[4][4] = {}, au[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += kFK) {
-    const float4 xa = *reinterpret_cast<const float4*>(p.act + arow * K + k0 + lk);
-    const float4 ga = *reinterpret_cast<const float4*>(wg + wrow * K + k0 + lk);
-    sX[lk + 0][lrow] = xa.x; sX[lk + 1][lrow] = xa.y; sX[lk + 2][lrow] = xa.z; sX[lk + 3][lrow] = xa.w;
-    sG[lk + 0][lrow] = ga.x; sG[lk + 1][lrow] = ga.y; sG[lk + 2][lrow] = ga.z; sG[lk + 3][lrow] = ga.w;
-    if (SWIGLU) {
-      const float4 ua = *reinterpret_cast<const float4*>(wu + wrow * K + k0 + lk);
-      sU[lk + 0][lrow] = ua.x; sU[lk + 1][lrow] = ua.y; sU[lk + 2][lrow] = ua.z; sU[lk + 3][lrow] = ua.w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < kFK; ++kk) {
-      float a[4], g[4], u[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sX[kk][ty * 4 + i];
-        g[i] = sG[kk][tx * 4 + i];
-        if (SWIGLU) u[i] = sU[kk][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          ag[i][j] = fmaf(a[i], g[j], ag[i][j]);
-          if (SWIGLU) au[i][j] = fmaf(a[i], u[j], au[i][j]);
-        }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = row0 + ty * 4 + i;
-    if (row >= row_end) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n < N) {
-        const float v = SWIGLU ? (ag[i][j] / (1.0f + expf(-ag[i][j]))) * au[i][j] : ag[i][j];
-        p.out[int64_t(row) * N + n] = v;
-      }
-    }
-  }
-}
-
 // One persistent workgroup per compute unit (fewer for small problems).
 int grid_for(int64_t upper_tiles, int num_cu) {
   const int64_t g = upper_tiles < num_cu ? upper_tiles : num_cu;
@@ -677,21 +591,6 @@ hipError_t launch_ffn_bf16(const uint16_t* act, const int32_t* gather, int64_t T
   const hipError_t err = launch_tail_reduce(partial, mtile_prefix, offsets, E, a2.ntiles, grid2, F / kBK, H,
                                             y_perm, true, s);
   if (err != hipSuccess) return err;
-  return hipGetLastError();
-}
-
-hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t* offsets, int64_t R,
-                          int E, int H, int F, const float* wg, const float* wu, const float* wd,
-                          float* y_perm, int32_t* mtile_prefix, float* h, hipStream_t s) {
-  MOE_LAUNCH("ffn_tile_prefix", tile_prefix_kernel, dim3(1), dim3(256), s, offsets, E, kFM, mtile_prefix,
-             static_cast<int32_t*>(nullptr));
-  const int64_t mtiles_upper = (R + int64_t(E) * (kFM - 1)) / kFM;
-  GemmArgsF a1{act, gather, wg, wu, h, offsets, mtile_prefix, E, H, F, (F + kFN - 1) / kFN};
-  MOE_LAUNCH("ffn_gemm1_gate_up", grouped_gemm_f32_kernel<true>, dim3(unsigned(mtiles_upper * a1.ntiles)),
-             dim3(256), s, a1);
-  GemmArgsF a2{h, nullptr, wd, nullptr, y_perm, offsets, mtile_prefix, E, F, H, (H + kFN - 1) / kFN};
-  MOE_LAUNCH("ffn_gemm2_down", grouped_gemm_f32_kernel<false>, dim3(unsigned(mtiles_upper * a2.ntiles)),
-             dim3(256), s, a2);
   return hipGetLastError();
 }
 

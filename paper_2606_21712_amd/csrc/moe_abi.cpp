@@ -165,7 +165,7 @@ moe_status run_ffn(const char* fn, const void* act, const int32_t* gather, int64
                                               H, F, static_cast<const float*>(w_gate),
                                               static_cast<const float*>(w_up),
                                               static_cast<const float*>(w_down), static_cast<float*>(y_perm),
-                                              prefix, static_cast<float*>(h), stream_of(stream)));
+                                              static_cast<float*>(h), stream_of(stream)));
   }
   hipError_t err;
   const int ncu = cu_count(&err);

@@ -71,7 +71,7 @@ hipError_t launch_ffn_mxfp8(const uint8_t* x, const uint8_t* xs, const int32_t* 
 
 hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t* offsets, int64_t R,
                           int E, int H, int F, const float* wg, const float* wu, const float* wd,
-                          float* y_perm, int32_t* mtile_prefix, float* h, hipStream_t s);
+                          float* y_perm, float* h, hipStream_t s);
 
 hipError_t launch_combine(const void* y_perm, const int32_t* dest, const float* w, const void* y_shared,
                           int64_t T, int k, int H, bool bf16, void* y, hipStream_t s);
