@@ -567,29 +567,36 @@ hipError_t launch_ffn_bf16(const uint16_t* act, const int32_t* gather, int64_t T
                            int64_t R, int E, int H, int F, const uint16_t* wg, const uint16_t* wu,
                            const uint16_t* wd, uint16_t* y_perm, int32_t* mtile_prefix, int32_t* queues,
                            uint16_t* h, float* partial, int num_cu, hipStream_t s) {
-  MOE_LAUNCH("ffn_tile_prefix", tile_prefix_kernel, dim3(1), dim3(256), s, offsets, E, kBMMax, mtile_prefix,
-             queues);
+  const bool stream1 = use_stream_gemm(R, E, F, true, false, num_cu);
+  const bool stream2 = use_stream_gemm(R, E, H, false, false, num_cu);
+  if (!stream1 || !stream2)
+    MOE_LAUNCH("ffn_tile_prefix", tile_prefix_kernel, dim3(1), dim3(256), s, offsets, E, kBMMax, mtile_prefix, queues);
   const int64_t mtiles_upper = (R + int64_t(E) * (kBM - 1)) / kBM;
-
-  const int64_t act_bytes = T * H * 2;
-  const bool wide = act_bytes >= (int64_t(1) << 31);
-  GemmArgs a1{queues, queues + 2, act, gather, wg, wu, h, nullptr, offsets, mtile_prefix, E, H, F, (F + 127) / 128,
-              int(R), wide ? 0 : int(act_bytes)};
-  const dim3 grid1(grid_for(mtiles_upper * a1.ntiles, num_cu));
-  if (gather != nullptr && wide)
-    MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_bf16_kernel<true, kTokensWide>), grid1, dim3(kGemmThreads), s,
-               a1);
-  else if (gather != nullptr)
-    MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_bf16_kernel<true, kTokens>), grid1, dim3(kGemmThreads), s, a1);
-  else
-    MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_bf16_kernel<true, kRows>), grid1, dim3(kGemmThreads), s, a1);
+  hipError_t err = hipSuccess;
+  if (stream1) {
+    err = launch_stream_gemm_bf16(act, gather, T, offsets, R, E, H, F, wg, wu, h, num_cu, s);
+    if (err != hipSuccess) return err;
+  } else {
+    const int64_t act_bytes = T * H * 2;
+    const bool wide = act_bytes >= (int64_t(1) << 31);
+    GemmArgs a1{queues, queues + 2, act, gather, wg, wu, h, nullptr, offsets, mtile_prefix, E, H, F, (F + 127) / 128,
+                int(R), wide ? 0 : int(act_bytes)};
+    const dim3 grid1(grid_for(mtiles_upper * a1.ntiles, num_cu));
+    if (gather != nullptr && wide)
+      MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_bf16_kernel<true, kTokensWide>), grid1, dim3(kGemmThreads), s,
+                 a1);
+    else if (gather != nullptr)
+      MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_bf16_kernel<true, kTokens>), grid1, dim3(kGemmThreads), s, a1);
+    else
+      MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_bf16_kernel<true, kRows>), grid1, dim3(kGemmThreads), s, a1);
+  }
+  if (stream2) return launch_stream_gemm_bf16(h, nullptr, R, offsets, R, E, F, H, wd, nullptr, y_perm, num_cu, s);
   GemmArgs a2{queues + 1, queues + 2 + kGroups, h, nullptr, wd, nullptr, y_perm, partial, offsets, mtile_prefix, E,
               F, H, (H + 255) / 256, int(R), 0};
   const int grid2 = grid_for(mtiles_upper * a2.ntiles, num_cu);
   MOE_LAUNCH("ffn_gemm2_down", (grouped_gemm_bf16_kernel<false, kRows>), dim3(grid2), dim3(kGemmThreads), s,
              a2);
-  const hipError_t err = launch_tail_reduce(partial, mtile_prefix, offsets, E, a2.ntiles, grid2, F / kBK, H,
-                                            y_perm, true, s);
+  err = launch_tail_reduce(partial, mtile_prefix, offsets, E, a2.ntiles, grid2, F / kBK, H, y_perm, true, s);
   if (err != hipSuccess) return err;
   return hipGetLastError();
 }

@@ -58,10 +58,9 @@ __global__ __launch_bounds__(kFThreads, 4) void grouped_gemm_f32_kernel(GemmArgs
     st0[tid] = 0;
     st1[tid] = 0;
   }
-  const int nt = int(blockIdx.x) % p.ntiles;
   MTile tile;
-  if (!locate_mtile<kFM>(p.offsets, p.E, int(blockIdx.x) / p.ntiles, &tile)) return;   // uniform across the block
-  const int e = tile.e, row0 = tile.row0, row_stop = tile.row_stop;
+  if (!locate_tile<kFM>(p.offsets, p.E, p.ntiles, int(blockIdx.x), &tile)) return;     // uniform across the block
+  const int e = tile.e, nt = tile.nt, row0 = tile.row0, row_stop = tile.row_stop;
   const int K = p.K, N = p.N;
   const int n0 = nt * (SWIGLU ? kFN / 2 : kFN);
 

@@ -30,38 +30,10 @@
 
 #include "common.h"
 #include "moe_internal.h"
+#include "mxfp8.h"
 
 namespace moe {
 namespace {
-
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-
-// ----------------------------------------------------------------------------- MXFP8 encoding
-// floor(log2 amax) - 8 clamped to [-127, 127]; amax >= 0 finite.  A zero or
-// subnormal amax (floor(log2) <= -127) clamps to -127.
-__device__ __forceinline__ int mx_shared_exp(float amax) {
-  const int ef = int((__float_as_uint(amax) >> 23) & 0xFFu);
-  if (ef == 0) return -127;
-  const int e = ef - 127 - 8;
-  return e < -127 ? -127 : (e > 127 ? 127 : e);
-}
-
-// 2^-se for se in [-127, 119] (always a normal float).
-__device__ __forceinline__ float mx_inv_scale(int se) { return __uint_as_float(uint32_t(127 - se) << 23); }
-
-// E4M3 codes of four values with |v| < 512, packed low byte first: the nearest
-// E4M3 value, ties to an even mantissa, magnitudes above 448 saturated to 448,
-// the sign bit kept (also for zero).  gfx950's v_cvt_pk_fp8_f32 converts to OCP
-// E4M3 rounding to nearest even; clamping to +-448 first gives the saturation.
-// For every fp32 input with |v| < 512 this yields the codes of the definition
-// (binade e = max(floor(log2 |v|), -6), spacing 2^(e-3), ties to even), which
-// was checked over all 2^31 such bit patterns.
-__device__ __forceinline__ uint32_t e4m3_pack4(float a, float b, float c, float d) {
-  auto sat = [](float v) { return __builtin_amdgcn_fmed3f(v, -448.0f, 448.0f); };
-  int w = __builtin_amdgcn_cvt_pk_fp8_f32(sat(a), sat(b), 0, false);
-  w = __builtin_amdgcn_cvt_pk_fp8_f32(sat(c), sat(d), w, true);
-  return uint32_t(w);
-}
 
 // ----------------------------------------------------------------------------- quantize rows
 // A block walks whole rows (grid-stride); each thread takes 8 consecutive
@@ -495,16 +467,26 @@ hipError_t launch_ffn_mxfp8(const uint8_t* x, const uint8_t* xs, const int32_t* 
                             const uint8_t* wgs, const uint8_t* wu, const uint8_t* wus, const uint8_t* wd,
                             const uint8_t* wds, uint16_t* y_perm, int32_t* mtile_prefix, int32_t* queues, uint8_t* h,
                             uint8_t* hs, float* partial, int num_cu, hipStream_t s) {
-  hipError_t err = launch_tile_prefix(offsets, E, kBM, mtile_prefix, queues, s);
+  const bool stream1 = use_stream_gemm(R, E, F, true, true, num_cu);
+  const bool stream2 = use_stream_gemm(R, E, H, false, true, num_cu);
+  hipError_t err = hipSuccess;
+  if (!stream1 || !stream2) err = launch_tile_prefix(offsets, E, kBM, mtile_prefix, queues, s);
   if (err != hipSuccess) return err;
   const int64_t mtiles_upper = (R + int64_t(E) * (kBM - 1)) / kBM;
-  GemmArgsF8 a1{queues, queues + 2, x, xs, gather, wg, wgs, wu, wus, h, hs, nullptr, nullptr, offsets, mtile_prefix,
-                E, H, F, F / 128, int(R), int(T)};
-  const dim3 grid1(grid_for(mtiles_upper * a1.ntiles, num_cu));
-  if (gather != nullptr)
-    MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_fp8_kernel<true, true>), grid1, dim3(kThreads), s, a1);
-  else
-    MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_fp8_kernel<true, false>), grid1, dim3(kThreads), s, a1);
+  if (stream1) {
+    err = launch_stream_gemm1_mxfp8(x, xs, gather, gather != nullptr ? T : R, offsets, R, E, H, F, wg, wgs, wu, wus, h,
+                                    hs, num_cu, s);
+    if (err != hipSuccess) return err;
+  } else {
+    GemmArgsF8 a1{queues, queues + 2, x, xs, gather, wg, wgs, wu, wus, h, hs, nullptr, nullptr, offsets, mtile_prefix,
+                  E, H, F, F / 128, int(R), int(T)};
+    const dim3 grid1(grid_for(mtiles_upper * a1.ntiles, num_cu));
+    if (gather != nullptr)
+      MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_fp8_kernel<true, true>), grid1, dim3(kThreads), s, a1);
+    else
+      MOE_LAUNCH("ffn_gemm1_gate_up", (grouped_gemm_fp8_kernel<true, false>), grid1, dim3(kThreads), s, a1);
+  }
+  if (stream2) return launch_stream_gemm2_mxfp8(h, hs, offsets, R, E, F, H, wd, wds, y_perm, num_cu, s);
   GemmArgsF8 a2{queues + 1, queues + 10, h, hs, nullptr, wd, wds, nullptr, nullptr, nullptr, nullptr, y_perm, partial, offsets,
                 mtile_prefix, E, F, H, (H + 255) / 256, int(R), 0};
   const int grid2 = grid_for(mtiles_upper * a2.ntiles, num_cu);

@@ -7,16 +7,23 @@ namespace moe {
 
 struct MTile {
   int e;          // expert
+  int nt;         // n-tile
   int row0;       // first grouped row of the tile
   int row_stop;   // end of the tile's rows
 };
 
-// m-tile q of the experts' tiles in order, ceil(rows / BM) tiles of BM rows each (the
-// last one shorter); false when there are not that many.  Wave-uniform q and result;
-// every lane of the wavefront must call it.  64 experts per pass: one load of their
-// offsets, a scan over the lanes, and a ballot for the lane whose tiles hold q.
+// Tile L of the experts' tiles in order: expert e has ceil(rows / BM) m-tiles, its 32-row
+// blocks shared out evenly among them (BM % 32 = 0, so none exceeds BM rows), times NT
+// n-tiles; false when there are not that many tiles.
+// Inside an expert, the m-tiles of one n-tile, which share its weight panel, come 8 tiles
+// apart, so that workgroups dealt round-robin to the 8 XCDs run them one after another on
+// the same XCD and its L2 serves the panel; 8 n-tiles run side by side.
+// Wave-uniform L and result; every lane of the wavefront must call it.  64 experts per
+// pass: one load of their offsets, a scan over the lanes, and a ballot for the lane whose
+// tiles hold L.
 template <int BM>
-__device__ __forceinline__ bool locate_mtile(const int32_t* __restrict__ offsets, int E, int q, MTile* t) {
+__device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E, int NT, int L, MTile* t) {
+  const int q = L / NT;
   const int lane = threadIdx.x & (kWave - 1);
   int before = 0;
   for (int c0 = 0; c0 < E; c0 += kWave) {
@@ -34,8 +41,17 @@ __device__ __forceinline__ bool locate_mtile(const int32_t* __restrict__ offsets
     if (hit != 0ull) {
       const int l = __builtin_ctzll(hit);
       t->e = c0 + l;
-      t->row0 = __builtin_amdgcn_readlane(beg, l) + (q - __builtin_amdgcn_readlane(first, l)) * BM;
-      t->row_stop = min(__builtin_amdgcn_readlane(end, l), t->row0 + BM);
+      const int mt_e = __builtin_amdgcn_readlane(mt, l);
+      const int local = L - __builtin_amdgcn_readlane(first, l) * NT;
+      const int group = local / (kNumXcd * mt_e);                 // of 8 n-tiles, fewer at the end
+      const int width = min(kNumXcd, NT - group * kNumXcd);
+      const int rem = local - group * kNumXcd * mt_e;
+      t->nt = group * kNumXcd + rem % width;
+      const int mt_i = rem / width;
+      const int row_beg = __builtin_amdgcn_readlane(beg, l), row_end = __builtin_amdgcn_readlane(end, l);
+      const int64_t nb = (row_end - row_beg + kTileRowBlock - 1) / kTileRowBlock;
+      t->row0 = row_beg + kTileRowBlock * int(mt_i * nb / mt_e);
+      t->row_stop = min(row_end, row_beg + kTileRowBlock * int((mt_i + 1) * nb / mt_e));
       return true;
     }
     before = __builtin_amdgcn_readlane(before + x, kWave - 1);

@@ -73,6 +73,22 @@ hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t
                           int E, int H, int F, const float* wg, const float* wu, const float* wd,
                           float* y_perm, float* h, hipStream_t s);
 
+// One GEMM of the grouped FFN for small expert groups, K wide with N outputs per row: the
+// weights streamed through a ring of LDS stages; no tile prefix, no scratch.
+// use_stream_gemm: whether it is the faster one.  bf16: w1 != null is GEMM-1 (gate, up),
+// else GEMM-2; gather as launch_ffn_bf16, act_rows the rows of act.
+bool use_stream_gemm(int64_t R, int E, int N, bool swiglu, bool fp8, int num_cu);
+hipError_t launch_stream_gemm_bf16(const uint16_t* act, const int32_t* gather, int64_t act_rows, const int32_t* offsets,
+                                   int64_t R, int E, int K, int N, const uint16_t* w0, const uint16_t* w1,
+                                   uint16_t* out, int num_cu, hipStream_t s);
+hipError_t launch_stream_gemm1_mxfp8(const uint8_t* x, const uint8_t* xs, const int32_t* gather, int64_t act_rows,
+                                     const int32_t* offsets, int64_t R, int E, int K, int N, const uint8_t* wg,
+                                     const uint8_t* wgs, const uint8_t* wu, const uint8_t* wus, uint8_t* h,
+                                     uint8_t* hs, int num_cu, hipStream_t s);
+hipError_t launch_stream_gemm2_mxfp8(const uint8_t* h, const uint8_t* hs, const int32_t* offsets, int64_t R, int E,
+                                     int K, int N, const uint8_t* wd, const uint8_t* wds, uint16_t* y, int num_cu,
+                                     hipStream_t s);
+
 hipError_t launch_combine(const void* y_perm, const int32_t* dest, const float* w, const void* y_shared,
                           int64_t T, int k, int H, bool bf16, void* y, hipStream_t s);
 

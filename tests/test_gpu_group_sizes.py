@@ -68,3 +68,120 @@ def test_f32_groups(counts, H, F):
         if hi > lo:
             ref, bound = ffn_bound(x[tok[lo:hi].long()].double(), *(t[e].double() for t in w), 0.0, 2.0 ** -24)
             assert ((y[lo:hi] - ref).abs() <= bound).all(), (e, hi - lo)
+
+
+# The streaming kernels pick tiles of 32, 64, 128 or 160 rows, one to four k groups and 64 to
+# 256 weight rows by the average group size and the number of tiles: (counts, H, F) that reach
+# each of them, with groups on and around the tile edges and F, H off the column tiles.
+STREAM = {
+    "decode_few": ([0, 1, 3, 0, 32, 33, 1], 192, 320),
+    "decode_k_groups": ([2, 1, 0, 5], 4160, 64),
+    "decode_many": ([1, 0, 16, 17, 31, 32, 33, 2] * 8, 2304, 576),
+    "mid64": ([63, 64, 65, 1, 0, 40, 20, 30] * 8, 2112, 960),
+    "mid64_few": ([63, 64, 65, 1, 0, 40], 320, 192),
+    "mid64_wide": ([30, 33, 64, 65, 20, 25, 31, 28] * 8, 4096, 2048),
+    "mid128": ([127, 128, 129, 1, 0, 64, 96, 97], 4160, 4160),
+    "mid128_half": ([127, 128, 129, 1, 0, 64, 96, 97], 4160, 1216),
+    "mid160": ([159, 160, 161, 95, 96, 97, 129, 128], 4160, 4160),
+    "mid160_half": ([159, 160, 161, 320, 321, 1, 100, 128], 3136, 1664),
+    "one_expert": ([577], 448, 320),
+}
+
+
+@pytest.mark.parametrize("name", list(STREAM))
+def test_bf16_stream(name):
+    check_bf16(name, *STREAM[name])
+
+
+def check_bf16(name, c, H, F):
+    log(f"[gpu] bf16 groups {name} H={H} F={F}")
+    x, w, tok, off = make(c, H, F, torch.bfloat16, 7)
+    dx, dw, dtok, doff = x.cuda(), [t.cuda() for t in w], tok.cuda(), off.cuda()
+    y = moe.moe_grouped_ffn_gather(dx, dtok, doff, *dw)
+    y2 = moe.moe_grouped_ffn(dx[dtok.long()].contiguous(), doff, *dw)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    y = y.cpu().double()
+    experts = [e for e in range(len(c)) if c[e]]
+    for e in experts[:24]:
+        lo, hi = int(off[e]), int(off[e + 1])
+        ref, bound = ffn_bound(x[tok[lo:hi].long()].double(), *(t[e].double() for t in w), 2.0 ** -9, 2.0 ** -24)
+        assert ((y[lo:hi] - ref).abs() <= bound).all(), (e, hi - lo)
+
+
+@pytest.mark.parametrize("name", ["decode_few", "decode_k_groups", "decode_many", "mid64", "mid64_few", "mid128",
+                                  "mid128_half", "mid160_half", "one_expert"])
+def test_mxfp8_stream(name):
+    c, H, F = STREAM[name]
+    check_mxfp8(name, c, (H + 127) // 128 * 128, (F + 127) // 128 * 128)
+
+
+# Groups on the edges of the large-batch kernels' m-tiles (256 and 320 rows).  On a device's
+# own compute units shapes this small take the streaming kernels; planned for four compute
+# units they take the large-batch ones.
+LARGE = [1, 64, 65, 256, 257, 300, 320, 321, 512, 576, 577, 0]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "mxfp8"])
+def test_large_kernel_edges(dtype):
+    moe.set_cu_budget(4)
+    try:
+        if dtype == "bf16":
+            check_bf16("large edges", LARGE, 320, 448)
+        else:
+            check_mxfp8("large edges", LARGE, 384, 640)
+    finally:
+        moe.set_cu_budget(0)
+
+
+def check_mxfp8(name, c, H, F):
+    """The reference is dequantized in float64; the MFMA's fp8 sums are within 2^-12 of the sum
+    of the products' magnitudes, and a code of h that rounds the other way moves it by at most
+    one part in eight (a scale by two)."""
+    log(f"[gpu] mxfp8 groups {name} H={H} F={F}")
+    x, w, tok, off = make(c, H, F, torch.bfloat16, 9)
+    dx, dtok, doff = x.cuda(), tok.cuda(), off.cuda()
+    dw = [moe.quantize_weights_mxfp8(t.cuda()) for t in w]
+    xq = moe.moe_quantize_mxfp8(dx)
+    y = moe.moe_grouped_ffn_mxfp8_gather(xq, dtok, doff, *dw)
+    y2 = moe.moe_grouped_ffn_mxfp8(moe.moe_quantize_mxfp8(dx, row_map=dtok), doff, *dw)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+    y = y.cpu().double()
+    X = dequantize(xq)
+    W = [dequantize(q).reshape(len(c), -1, q.codes.shape[-1]) for q in dw]
+    experts = [e for e in range(len(c)) if c[e]]
+    for e in experts[:24]:
+        lo, hi = int(off[e]), int(off[e + 1])
+        xe = X[tok[lo:hi].long()]
+        g, u = xe @ W[0][e].T, xe @ W[1][e].T
+        h = g * torch.sigmoid(g) * u
+        y64 = quantize64(h) @ W[2][e].T
+        # as a whole: rounding differences of h are rare and independent
+        rel = (y[lo:hi] - y64).norm() / y64.norm()
+        assert rel <= 1e-2, (e, hi - lo, float(rel))
+        # and no single value off by more than every h code moving one step, each way at random
+        # (six sigma), plus the sums' and the store's rounding
+        step = (h.abs().square() @ W[2][e].square().T).sqrt() / 8
+        bound = 6 * step * 0.25 + 2.0 ** -12 * (h.abs() @ W[2][e].abs().T) + 2.0 ** -8 * y64.abs() + 1e-6
+        assert ((y[lo:hi] - y64).abs() <= bound).all(), (e, hi - lo)
+
+
+def dequantize(q):
+    """float64 values of an MXFP8 matrix (codes E4M3, scales [K / 128][rows][4])."""
+    codes = q.codes.reshape(-1, q.codes.shape[-1]).cpu()
+    rows, K = codes.shape
+    v = codes.view(torch.float8_e4m3fn).double()
+    s = q.scales[: rows * K // 32].cpu().reshape(K // 128, rows, 4).permute(1, 0, 2).reshape(rows, K // 32).double()
+    return (v.reshape(rows, K // 32, 32) * torch.exp2(s - 127.0)[..., None]).reshape(rows, K)
+
+
+def quantize64(v):
+    """v rounded to MXFP8 and back, in float64."""
+    b = v.reshape(-1, 32)
+    amax = b.abs().amax(1, keepdim=True)
+    s = torch.exp2(torch.where(amax > 0, (torch.frexp(amax)[1].double() - 9.0).clamp(-127, 127),
+                               torch.full_like(amax, -127.0)))
+    q = b / s
+    step = torch.exp2((torch.frexp(q)[1].double() - 1.0).clamp_min(-6.0) - 3.0)
+    return ((torch.round(q / step) * step).clamp(-448.0, 448.0) * s).reshape(v.shape)
