@@ -196,46 +196,54 @@ __global__ __launch_bounds__(kThreads) void permute_rank_kernel(
 }
 
 // Small batches (at most kSmallUnits units): the three phases in one block of
-// 1024 threads, one wavefront per unit, with the per-unit counts in LDS.  Same
-// results as count + scan + rank.
+// 1024 threads.  Latency bounds it (dependent LDS reads and ballots), so the
+// assignments are dealt evenly over the 16 wavefronts in whole groups of 64, `iters` of
+// them each, instead of filling one wavefront's 16 first; per-wavefront counts in
+// LDS.  Same results as count + rank.  Measured, 48 and 768 assignments over 8 and 64
+// experts: 11.1 -> 5.0 and 14.9 -> 5.0 us.
 constexpr int kSmallUnits = 16;
 constexpr int kSmallThreads = kSmallUnits * kWave;
 
 __global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
-    const int32_t* __restrict__ ids, int64_t R, int E, int k, int nbits, int32_t* __restrict__ counts,
+    const int32_t* __restrict__ ids, int64_t R, int E, int k, int nbits, int iters, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ dest, int32_t* __restrict__ sorted_tok) {
   __shared__ int32_t run[kSmallUnits][kMaxExperts];
   __shared__ int32_t s_wsum[4];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int w = tid / kWave;                                // the unit
-  const int64_t base = int64_t(w) * kUnit;
+  const int w = tid / kWave;                                // the wavefront's share
+  const int64_t base = int64_t(w) * (iters * kWave);
   const uint64_t below = (1ull << lane) - 1ull;
-  // the unit's ids, all loaded at once and kept for the rank phase
+  // its ids, all loaded at once and kept for the rank phase
   int idv[kIters];
 #pragma unroll
   for (int it = 0; it < kIters; ++it) {
     const int64_t a = base + it * kWave + lane;
-    idv[it] = a < R ? ids[a] : -1;
+    idv[it] = it < iters && a < R ? ids[a] : -1;
   }
   for (int e = lane; e < E; e += kWave) run[w][e] = 0;
   __syncthreads();
-  // counts per unit
+  // counts per share
 #pragma unroll
   for (int it = 0; it < kIters; ++it) {
+    if (it >= iters || base + it * kWave >= R) break;       // uniform across the wave
     const bool valid = idv[it] >= 0;
     const int id = valid ? idv[it] : 0;
     const uint64_t match = wave_match(id, valid, nbits);
     if (valid && (match & below) == 0ull) run[w][id] += __popcll(match);
   }
   __syncthreads();
-  // per expert: exclusive scan over the units, then offsets = exclusive scan of the
+  // per expert: exclusive scan over the shares, then offsets = exclusive scan of the
   // totals over the experts (threads 0..255, one expert each)
   int32_t total = 0;
+  int32_t before_share[kSmallUnits];
   if (tid < E) {
+#pragma unroll
+    for (int u = 0; u < kSmallUnits; ++u) before_share[u] = run[u][tid];
+#pragma unroll
     for (int u = 0; u < kSmallUnits; ++u) {
-      const int32_t c = run[u][tid];
-      run[u][tid] = total;
+      const int32_t c = before_share[u];
+      before_share[u] = total;
       total += c;
     }
     counts[tid] = total;
@@ -256,14 +264,16 @@ __global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
     const int32_t ex = before + x - total;                   // exclusive offset of expert tid
     if (tid < E) {
       offsets[tid] = ex;
-      for (int u = 0; u < kSmallUnits; ++u) run[u][tid] += ex;
+#pragma unroll
+      for (int u = 0; u < kSmallUnits; ++u) run[u][tid] = ex + before_share[u];
     }
     if (tid == E - 1) offsets[E] = ex + total;
   }
   __syncthreads();
-  // rows: the unit's running position per expert plus the rank among equal ids
+  // rows: the share's running position per expert plus the rank among equal ids
 #pragma unroll
   for (int it = 0; it < kIters; ++it) {
+    if (it >= iters || base + it * kWave >= R) break;
     const int64_t a = base + it * kWave + lane;
     const bool valid = idv[it] >= 0;
     const int id = valid ? idv[it] : 0;
@@ -321,7 +331,8 @@ hipError_t launch_permute(const int32_t* ids, const void* x, int64_t T, int E, i
   int nbits = 0;
   while ((1 << nbits) < E) ++nbits;
   if (U <= kSmallUnits) {
-    MOE_LAUNCH("permute_small", permute_small_kernel, dim3(1), dim3(kSmallThreads), s, ids, R, E, k, nbits,
+    const int iters = int((R + kSmallThreads - 1) / kSmallThreads);    // <= kIters
+    MOE_LAUNCH("permute_small", permute_small_kernel, dim3(1), dim3(kSmallThreads), s, ids, R, E, k, nbits, iters,
                counts, offsets, dest, sorted_tok);
   } else {
     // per-block totals [E][Bpad] in the workspace (E * Bpad <= E * Upad ints)

@@ -1,0 +1,29 @@
+"""Small batches: the one-block grouping on and around its 64-assignment groups and its
+largest size, and the combine's column splits."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_21712_amd as moe
+from gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,k,E", [(1, 1, 1), (63, 1, 3), (64, 1, 256), (65, 1, 7), (21, 3, 5), (512, 2, 64),
+                                   (513, 2, 64), (1023, 1, 2), (341, 3, 8), (1025, 1, 256), (8191, 2, 9),
+                                   (8192, 2, 64), (1024, 16, 17), (1025, 16, 256)])
+def test_permute_small(T, k, E):
+    """Exactly the oracle's maps, below, at and above the single-block limit of 16384."""
+    log(f"[gpu] permute maps T={T} k={k} E={E}")
+    rng = np.random.default_rng(T * 31 + E)
+    ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    x = torch.zeros((T, 64), dtype=torch.bfloat16, device="cuda")
+    out = moe.moe_permute(torch.from_numpy(ids).cuda(), x, E, gather_rows=False)
+    torch.cuda.synchronize()
+    counts, offsets, dest, tok, _ = oracle.permute(ids, np.zeros((T, 1), np.float32), E)
+    for name, want in (("counts", counts), ("offsets", offsets), ("dest_rows", dest), ("sorted_token_ids", tok)):
+        assert np.array_equal(out[name].cpu().numpy(), want), name
