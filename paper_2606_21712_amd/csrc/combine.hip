@@ -186,10 +186,14 @@ hipError_t launch_combine(const void* y_perm, const int32_t* dest, const float* 
   // Column split: a token's row is cut into `splits` parts, one wavefront each, so
   // that large batches run enough wavefronts with a few vectors per lane each
   // (measured cold, % of 8 TB/s: memory-constrained 71 -> 76 with 2 parts,
-  // Mixtral-shaped 32K tokens 75 -> 77 with 4, DeepSeek-shaped 65 -> 70 with 8);
-  // small batches (fewer than 8192 tokens) keep whole rows.
+  // Mixtral-shaped 32K tokens 75 -> 77 with 4, DeepSeek-shaped 65 -> 70 with 8).
+  // Up to 4096 wavefronts the latency of a row bounds it: as many parts as leave each
+  // lane a vector (96 tokens, k 8, H 7168: 18.1 -> 5.8 us).
+  // Batches between (4096 to 8192 tokens) keep whole rows.
   int splits = 1;
-  if (T >= 8192)
+  if (T < 4096)
+    while (splits < 16 && nvec / (2 * splits) >= kWave && T * (2 * splits) <= 4096) splits *= 2;
+  else if (T >= 8192)
     while (splits < 8 && nvec / (2 * splits) >= kWave && T * splits < (int64_t(1) << 30) &&
            (nvec / splits > 4 * kWave || T * splits < 131072))
       splits *= 2;

@@ -27,3 +27,24 @@ def test_permute_small(T, k, E):
     counts, offsets, dest, tok, _ = oracle.permute(ids, np.zeros((T, 1), np.float32), E)
     for name, want in (("counts", counts), ("offsets", offsets), ("dest_rows", dest), ("sorted_token_ids", tok)):
         assert np.array_equal(out[name].cpu().numpy(), want), name
+
+
+@pytest.mark.parametrize("T,k,H,dt", [(1, 1, 64, torch.bfloat16), (1, 8, 7168, torch.bfloat16),
+                                      (97, 8, 7168, torch.bfloat16), (255, 2, 4096, torch.bfloat16),
+                                      (1000, 3, 4160, torch.bfloat16), (2049, 4, 1088, torch.bfloat16),
+                                      (4095, 2, 2112, torch.bfloat16), (300, 2, 8256, torch.float32),
+                                      (33, 16, 320, torch.float32)])
+def test_combine_small(T, k, H, dt):
+    """Each output in float64, within k roundings of the fp32 sum and one of the store."""
+    log(f"[gpu] combine T={T} k={k} H={H} {dt}")
+    g = torch.Generator().manual_seed(T + k)
+    yp = torch.randn(T * k, H, generator=g).to(dt)
+    dest = torch.randperm(T * k, generator=g).to(torch.int32).reshape(T, k)
+    w = torch.rand(T, k, generator=g)
+    ys = torch.randn(T, H, generator=g).to(dt)
+    y = moe.moe_combine(yp.cuda(), dest.cuda(), w.cuda(), ys.cuda()).cpu().double()
+    rows = yp[dest.long()].double() * w.double()[..., None]
+    ref = rows.sum(1) + ys.double()
+    mag = rows.abs().sum(1) + ys.double().abs()
+    bound = (k + 2) * 2.0 ** -24 * mag + (2.0 ** -8 if dt == torch.bfloat16 else 2.0 ** -23) * ref.abs()
+    assert ((y - ref).abs() <= bound).all()
