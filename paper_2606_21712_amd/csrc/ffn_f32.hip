@@ -161,10 +161,10 @@ hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t
                           float* y_perm, float* h, hipStream_t s) {
   const int64_t mtiles_upper = (R + int64_t(E) * (kFM - 1)) / kFM;
   GemmArgsF a1{act, gather, wg, wu, h, offsets, E, H, F, F / (kFN / 2)};
-  MOE_LAUNCH("ffn_gemm1_gate_up", grouped_gemm_f32_kernel<true>, dim3(unsigned(mtiles_upper * a1.ntiles)),
+  MOE_LAUNCH("ffn_gemm1_gate_up", grouped_gemm_f32_kernel<true>, dim3(tile_grid(mtiles_upper * a1.ntiles)),
              dim3(kFThreads), s, a1);
   GemmArgsF a2{h, nullptr, wd, nullptr, y_perm, offsets, E, F, H, H / kFN};
-  MOE_LAUNCH("ffn_gemm2_down", grouped_gemm_f32_kernel<false>, dim3(unsigned(mtiles_upper * a2.ntiles)),
+  MOE_LAUNCH("ffn_gemm2_down", grouped_gemm_f32_kernel<false>, dim3(tile_grid(mtiles_upper * a2.ntiles)),
              dim3(kFThreads), s, a2);
   return hipGetLastError();
 }

@@ -13,9 +13,18 @@
 //     streams while the other starts or finishes a tile; groups of more rows take eight
 //     wavefronts and 256 weight rows, so that the activation rows, which come from L2
 //     for every tile, stay the smaller part of the traffic;
-//   - a tile starts its k loop at a step of its own, so that the tiles in flight do not
-//     all ask the same HBM channels (row pitches are multiples of the channel stride);
-//     tiles that share a weight panel (the m-tiles of one expert) start together;
+//   - tiles start their k loops at different steps, so that the tiles in flight do not
+//     all ask the same HBM channels (row pitches are multiples of the channel stride).
+//     Eight neighbouring n-tiles of an expert start together: an XCD's L2 then serves
+//     them one activation panel (and the m-tiles of one n-tile its weight panel).  Mixtral
+//     shape, down projection at 127 rows: 258 us with a start of each tile's own, 207 with
+//     these; 256 tokens over 64 experts of H 4096, F 4096, both GEMMs: 1018 and 959;
+//   - weights that one m-tile reads bypass the caches (nt): nothing reads them again soon,
+//     and without the allocation HBM delivers 6.4 to 6.9 TB/s instead of 5.8 to 6.1.  DeepSeek shape at
+//     12 rows, both GEMMs: 933 -> 842 us; Mixtral shape at 6 rows: 471 -> 428.  Not for
+//     small weights (a GEMM's under 128 MB, which the Infinity Cache may hold from one
+//     call to the next: a shared expert's 58 MB at 8 rows 22 us, 28 bypassed), and not for
+//     groups of several m-tiles (600 rows: 77 us, 100);
 //   - no tile prefix, counters or persistent loop: a workgroup finds its tile from the
 //     device-side offsets, the grid holds the host's bound on the tiles.
 // The operands, their LDS layout and the MFMA instructions are those of the large-batch
@@ -25,6 +34,7 @@
 #include <type_traits>
 
 #include "group_locate.h"
+#include "lds_stage.h"
 #include "moe_internal.h"
 #include "mxfp8.h"
 
@@ -49,27 +59,12 @@ struct StreamArgs {
   int E, K, N, ntiles, R;
 };
 
-// gfx9 s_waitcnt immediate with only vmcnt(n).
-constexpr int wait_vm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
-
-// An offset into a stage's LDS object that the compiler keeps as one value.  It tells a
-// stage's reads from the loads in flight to the others by the object that an address comes
-// from, and loses that through more than a few additions: it would then wait for every load.
-__device__ __forceinline__ int opaque_v(int x) {
-  asm("" : "+v"(x));
-  return x;
-}
-__device__ __forceinline__ int opaque_s(int x) {
-  asm("" : "+s"(x));
-  return x;
-}
-
 // 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7): conflict-free operand reads.
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
 // 2 x WN wavefronts: each MR / 2 activation rows x 64 weight rows of the tile (GEMM-1: 32
 // gate and 32 up rows of the same features).  MR: activation rows per tile; S: stages.
-template <bool FP8, bool SWIGLU, int WN, int MR, int KG, int S>
+template <bool FP8, bool SWIGLU, int WN, int MR, int KG, int S, bool NTW>
 __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArgs p) {
   constexpr int kElt = FP8 ? 1 : 2;
   constexpr int kBN = 64 * WN;                       // weight rows of the tile
@@ -169,8 +164,7 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
       soff = kASOff + c * 256;
     }
   }
-  // the m-tiles of an expert share a weight panel: one start for all of them
-  const int krot = int((int64_t(e) * p.ntiles + nt) * 7 % KT);
+  const int krot = int((int64_t(e) * ((p.ntiles + 7) / 8) + nt / 8) * 7 % KT);
   const int wdst = opaque_s(gbase + wave * 1024);
   soff = opaque_s(gbase + soff);
   auto issue = [&](uint8_t* stage, int it) {         // k step it * KG + kg, or the last one past the end
@@ -180,7 +174,7 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds((SWIGLU && i >= 2) ? rw1 : rw0, stage + (wdst + kWaves * i * 1024),
-                                               16, woff[i], kb, 0, 0);
+                                               16, woff[i], kb, 0, NTW ? 2 : 0);
 #pragma unroll
     for (int i = 0; i < kAPass; ++i)
       __builtin_amdgcn_global_load_lds(aptr[i] + kb, stage + adst[i], 16, 0, 0);
@@ -284,10 +278,7 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
     auto step = [&](const uint8_t* cur, uint8_t* nxt, int it) {
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_waitcnt(wait_vm((S - 2) * kLoads));
-      // a bare barrier: __syncthreads would wait for every load still in flight
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
+      bare_barrier();
       __builtin_amdgcn_sched_barrier(0);
       issue(nxt, it + S - 1);
       __builtin_amdgcn_sched_barrier(0);
@@ -398,15 +389,6 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
   }
 }
 
-template <bool FP8, bool SWIGLU, int WN, int MR, int KG, int S>
-void launch_tiles(const char* name, StreamArgs a, hipStream_t s) {
-  const int cols = 64 * WN / (SWIGLU ? 2 : 1);
-  a.ntiles = (a.N + cols - 1) / cols;
-  const int64_t mtiles = (int64_t(a.R) + int64_t(std::min(a.E, a.R)) * (MR - 1)) / MR;
-  MOE_LAUNCH(name, (stream_gemm_kernel<FP8, SWIGLU, WN, MR, KG, S>), dim3(unsigned(mtiles * a.ntiles)),
-             dim3(128 * WN * KG), s, a);
-}
-
 // Experts that R rows dealt evenly at random reach, and their average rows.
 struct Load {
   double live;
@@ -414,6 +396,19 @@ struct Load {
   Load(int64_t R, int E)
       : live(E > 1 ? E * -std::expm1(double(R) * std::log1p(-1.0 / E)) : 1.0), rows(int64_t(double(R) / live + 0.999)) {}
 };
+
+template <bool FP8, bool SWIGLU, int WN, int MR, int KG, int S>
+void launch_tiles(const char* name, StreamArgs a, hipStream_t s) {
+  const int cols = 64 * WN / (SWIGLU ? 2 : 1);
+  a.ntiles = (a.N + cols - 1) / cols;
+  const int64_t mtiles = (int64_t(a.R) + int64_t(std::min(a.E, a.R)) * (MR - 1)) / MR;
+  const int64_t weight_bytes = int64_t(a.E) * a.N * a.K * (FP8 ? 1 : 2) * (SWIGLU ? 2 : 1);
+  const dim3 grid(tile_grid(mtiles * a.ntiles)), block(128 * WN * KG);
+  if (weight_bytes >= (int64_t(128) << 20) && Load(a.R, a.E).rows <= MR)
+    MOE_LAUNCH(name, (stream_gemm_kernel<FP8, SWIGLU, WN, MR, KG, S, true>), grid, block, s, a);
+  else
+    MOE_LAUNCH(name, (stream_gemm_kernel<FP8, SWIGLU, WN, MR, KG, S, false>), grid, block, s, a);
+}
 
 // Workgroups of a launch with WN, MR at that load.
 template <bool SWIGLU>
@@ -425,13 +420,9 @@ int64_t workgroups(const StreamArgs& a, const Load& l, int WN, int MR) {
 // Which tile.  More activation rows per tile read the weights fewer times and the
 // activations less often, fewer give more workgroups; the lines lie where the mean group
 // leaves its largest members inside one tile (a group cut in two reads its weights from L2
-// twice).  Measured, us of one GEMM (M: H 4096, F 14336, 8 experts; D: H 7168, F 2048, 64):
+// twice).  Measured, us of one GEMM (M: H 4096, F 14336, 8 experts):
 //   160 rows for means of 100 to 320: M down at 256 rows 289 (128 rows: 430); beyond that
-//     128 rows (one expert, 2048 rows, gate/up: 114, 160 rows: 191);
-//   256 weight rows and one workgroup of eight wavefronts per compute unit once there are
-//     3.5 rounds of them: D down at 12 rows 329 (128 weight rows, two workgroups: 374), but
-//     128 experts of F 768 at 6 rows, three rounds: 204 (193); MXFP8 is the faster with two
-//     workgroups throughout (D at 25 rows 509 and 511 both GEMMs);
+//     128 rows (one expert, 2048 rows, H 7168, F 2048, gate/up: 114, 160 rows: 191);
 //   fewer workgroups than two per compute unit: two k groups, which keep as many bytes in
 //     flight on half the workgroups (M down at one row: 80 -> 52), and four on 64 weight
 //     rows when even that leaves half the chip idle (one expert, F 2048, H 7168 at 8 rows,
@@ -450,7 +441,6 @@ void launch_gemm(const char* name, const StreamArgs& a, int num_cu, hipStream_t 
     if (wg(4, 128) >= num_cu) return launch_tiles<FP8, SWIGLU, 4, 128, 1, 3>(name, a, s);
     if (wg(2, 128) >= num_cu * 3 / 4) return launch_tiles<FP8, SWIGLU, 2, 128, 1, 4>(name, a, s);
   }
-  if (!FP8 && 2 * wg(4, 64) >= 7 * num_cu) return launch_tiles<FP8, SWIGLU, 4, 64, 1, 3>(name, a, s);
   if (l.rows <= 16) {
     if (wg(2, 32) >= 2 * num_cu) launch_tiles<FP8, SWIGLU, 2, 32, 1, 3>(name, a, s);
     else if (wg(2, 32) >= num_cu / 2) launch_tiles<FP8, SWIGLU, 2, 32, 2, 3>(name, a, s);
@@ -464,20 +454,24 @@ void launch_gemm(const char* name, const StreamArgs& a, int num_cu, hipStream_t 
 
 }  // namespace
 
-// Against the large-batch kernels, us of the FFN, here (there):
-//   D bf16 at 12 rows 936 (1006), 64 rows 1000 (1061), 128 rows 1141 (1183); M bf16 at 6 rows
-//   483 (657), 64 rows 538 (738), 127 rows 644 (809), 256 rows gate/up 597 (569);
-//   D MXFP8 at 25 rows 507 (569), 100 rows 580 (632), 128 rows 709 (674); M MXFP8 at 6 rows
-//   248 (373), 127 rows 378 (418).
-// Few tiles leave the large-batch kernels' grid part empty, there the line lies further out:
-// M down at 256 rows, 128 tiles: 289 (389); one expert, F 2048, 2048 rows, gate/up, 112
-// tiles: 114 (159); but 16 experts of H 2048, F 1408 at 250 rows, 176 tiles: 83 (69).
+// Against the large-batch kernels, us of the FFN, here (there).  M as above, D: H 7168,
+// F 2048, 64 experts; C: H 4096, F 4096, 64 experts.
+//   bf16: M at 6 rows 427 (660), 64 rows 484 (745), 127 rows 590 (804), 175 rows gate/up 532
+//   (522); D at 12 rows 838 (1005), 64 rows 943 (1061), 128 rows 1123 (1189); C at 16 rows 954
+//   (1091), 128 rows 1249 (1361), but 1500 (1440) when the loads are lognormal (sigma 1):
+//   uneven groups have more tiles than their mean says, so the line lies below that;
+//   MXFP8: D at 25 rows 471 (567), 100 rows 627 (632), 128 rows 721 (669); M at 6 rows 217
+//   (374), 64 rows 267 (392), 127 rows 413 (418).
+// Few tiles leave the large-batch kernels' grid part empty; there the line lies further out:
+// M bf16 at 127 rows, 896 tiles; M down at 256 rows, 128 tiles: 286 (386); one expert, F 2048,
+// H 7168, 2048 rows, gate/up, 112 tiles: 118 (166); but 16 experts of H 2048, F 1408 at 250
+// rows, 176 tiles: 85 (71).
 bool use_stream_gemm(int64_t R, int E, int N, bool swiglu, bool fp8, int num_cu) {
   const Load l(R, E);
-  if (l.rows <= (fp8 ? 112 : 144)) return true;
+  if (l.rows <= (fp8 ? 96 : 112)) return true;
   const int cols = swiglu ? kTileCols / 2 : kTileCols;
   const int64_t big = int64_t(l.live * double((l.rows + kTileRowsMax - 1) / kTileRowsMax) * double((N + cols - 1) / cols));
-  return 2 * big <= num_cu || (l.rows <= 144 && big < 4 * num_cu);
+  return 2 * big <= num_cu || (!fp8 && l.rows <= 144 && big < 4 * num_cu);
 }
 
 hipError_t launch_stream_gemm_bf16(const uint16_t* act, const int32_t* gather, int64_t act_rows, const int32_t* offsets,

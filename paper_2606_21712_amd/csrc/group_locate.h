@@ -12,30 +12,44 @@ struct MTile {
   int row_stop;   // end of the tile's rows
 };
 
-// Tile L of the experts' tiles in order: expert e has ceil(rows / BM) m-tiles, its 32-row
-// blocks shared out evenly among them (BM % 32 = 0, so none exceeds BM rows), times NT
-// n-tiles; false when there are not that many tiles.
-// Inside an expert, the m-tiles of one n-tile, which share its weight panel, come 8 tiles
-// apart, so that workgroups dealt round-robin to the 8 XCDs run them one after another on
-// the same XCD and its L2 serves the panel; 8 n-tiles run side by side.
-// Wave-uniform L and result; every lane of the wavefront must call it.  64 experts per
+// The tile of workgroup b, false when it has none.  Expert e has ceil(rows / BM) m-tiles,
+// its 32-row blocks shared out evenly among them (BM % 32 = 0, so none exceeds BM rows),
+// times NT n-tiles; tiles are listed by expert, n-tile, m-tile, and workgroups, dealt
+// round-robin to the 8 XCDs (b on XCD b % 8), take that list in eight contiguous parts:
+// an XCD's workgroups share one expert's activation rows (and the m-tiles of one n-tile
+// its weight panel) through its L2.
+// Wave-uniform b and result; every lane of the wavefront must call it.  64 experts per
 // pass: one load of their offsets, a scan over the lanes, and a ballot for the lane whose
-// tiles hold L.
+// tiles hold the workgroup's.
 template <int BM>
-__device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E, int NT, int L, MTile* t) {
-  const int q = L / NT;
+__device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E, int NT, int b, MTile* t) {
   const int lane = threadIdx.x & (kWave - 1);
-  int before = 0;
-  for (int c0 = 0; c0 < E; c0 += kWave) {
+  int beg = 0, end = 0, mt = 0, x = 0;
+  auto scan = [&](int c0) {          // the m-tiles of 64 experts, and their inclusive sum
     const int i = c0 + lane;
-    const int beg = offsets[min(i, E)], end = offsets[min(i + 1, E)];   // equal past the last expert
-    const int mt = (end - beg + BM - 1) / BM;
-    int x = mt;
+    beg = offsets[min(i, E)];
+    end = offsets[min(i + 1, E)];    // equal past the last expert
+    mt = (end - beg + BM - 1) / BM;
+    x = mt;
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
       const int y = __shfl_up(x, d);
       if (lane >= d) x += y;
     }
+  };
+  int mtiles = 0;
+  for (int c0 = 0; c0 < E; c0 += kWave) {
+    scan(c0);
+    mtiles += __builtin_amdgcn_readlane(x, kWave - 1);
+  }
+  const int total = mtiles * NT;
+  const int per = (total + kNumXcd - 1) / kNumXcd;
+  const int L = (b % kNumXcd) * per + b / kNumXcd;
+  if (b / kNumXcd >= per || L >= total) return false;
+  const int q = L / NT;
+  int before = 0;
+  for (int c0 = 0; c0 < E; c0 += kWave) {
+    if (E > kWave) scan(c0);
     const int first = before + x - mt;
     const uint64_t hit = __ballot(q >= first && q < first + mt);
     if (hit != 0ull) {
@@ -43,11 +57,8 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
       t->e = c0 + l;
       const int mt_e = __builtin_amdgcn_readlane(mt, l);
       const int local = L - __builtin_amdgcn_readlane(first, l) * NT;
-      const int group = local / (kNumXcd * mt_e);                 // of 8 n-tiles, fewer at the end
-      const int width = min(kNumXcd, NT - group * kNumXcd);
-      const int rem = local - group * kNumXcd * mt_e;
-      t->nt = group * kNumXcd + rem % width;
-      const int mt_i = rem / width;
+      t->nt = local / mt_e;
+      const int mt_i = local % mt_e;
       const int row_beg = __builtin_amdgcn_readlane(beg, l), row_end = __builtin_amdgcn_readlane(end, l);
       const int64_t nb = (row_end - row_beg + kTileRowBlock - 1) / kTileRowBlock;
       t->row0 = row_beg + kTileRowBlock * int(mt_i * nb / mt_e);
@@ -58,5 +69,8 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
   }
   return false;
 }
+
+// Workgroups that cover `tiles` tiles in eight parts.
+inline unsigned tile_grid(int64_t tiles) { return unsigned((tiles + kNumXcd - 1) / kNumXcd * kNumXcd); }
 
 }  // namespace moe
