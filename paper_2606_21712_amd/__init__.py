@@ -115,13 +115,16 @@ def _check(status: int):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # a plain int: the argtypes convert it in C.  A c_void_p made here doubles the cost, 0.21 ->
+    # 0.43 us for each of a layer step's some 30 pointers: with the stream looked up once, a
+    # step's calls are enqueued in 25 us, 32 before (24 tokens, 8 experts, top-2)
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream, device):
     if stream is None:
         stream = torch.cuda.current_stream(device)
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dt(t: torch.Tensor) -> int:
@@ -134,10 +137,11 @@ def _dt(t: torch.Tensor) -> int:
 
 def _dev(*ts):
     for t in ts:
-        if t is not None and not t.is_cuda:
-            raise ValueError("all tensors must be on the GPU")
-        if t is not None and not t.is_contiguous():
-            raise ValueError("all tensors must be contiguous")
+        if t is not None:
+            if not t.is_cuda:
+                raise ValueError("all tensors must be on the GPU")
+            if not t.is_contiguous():
+                raise ValueError("all tensors must be contiguous")
 
 
 # --------------------------------------------------------------------------- the four calls
@@ -429,6 +433,8 @@ class MoELayer:
 
     def run(self, x, logits, w_gate, w_up, w_down, ws_gate=None, ws_up=None, ws_down=None,
             renormalize=1, stream=None):
+        if stream is None and x.is_cuda:   # looked up once, not in each of the calls
+            stream = torch.cuda.current_stream(x.device)
         moe_route(logits, self.k, renormalize, self.topk_ids, self.topk_weights, stream=stream)
         moe_permute(self.topk_ids, x, self.E, out=self.perm, ws=self.ws_perm, stream=stream)
         if self.gather:
@@ -517,6 +523,8 @@ class MoELayerMXFP8:
 
     def run(self, x, logits, wq_gate, wq_up, wq_down, wqs_gate=None, wqs_up=None, wqs_down=None,
             renormalize=1, stream=None):
+        if stream is None and x.is_cuda:   # looked up once, not in each of the calls
+            stream = torch.cuda.current_stream(x.device)
         moe_route(logits, self.k, renormalize, self.topk_ids, self.topk_weights, stream=stream)
         moe_permute(self.topk_ids, x, self.E, out=self.perm, ws=self.ws_perm, stream=stream)
         if self.gather:
