@@ -160,16 +160,16 @@ moe_status run_ffn(const char* fn, const void* act, const int32_t* gather, int64
   auto* prefix = static_cast<int32_t*>(ws);
   auto* queues = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(ws) + moe::ffn_queue_offset(E));
   void* h = static_cast<uint8_t*>(ws) + moe::ffn_h_offset(E);
+  hipError_t err;
+  const int ncu = cu_count(&err);
+  if (err != hipSuccess) return hip_status(fn, err);
   if (dt == MOE_DTYPE_F32) {
     return hip_status(fn, moe::launch_ffn_f32(static_cast<const float*>(act), gather, expert_offsets, R, E,
                                               H, F, static_cast<const float*>(w_gate),
                                               static_cast<const float*>(w_up),
                                               static_cast<const float*>(w_down), static_cast<float*>(y_perm),
-                                              static_cast<float*>(h), stream_of(stream)));
+                                              static_cast<float*>(h), ncu, stream_of(stream)));
   }
-  hipError_t err;
-  const int ncu = cu_count(&err);
-  if (err != hipSuccess) return hip_status(fn, err);
   auto* partial = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + moe::ffn_partial_offset(R, E, F, dt));
   return hip_status(
       fn, moe::launch_ffn_bf16(static_cast<const uint16_t*>(act), gather, T, expert_offsets, R, E, H, F,

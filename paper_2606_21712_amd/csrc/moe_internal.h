@@ -71,7 +71,7 @@ hipError_t launch_ffn_mxfp8(const uint8_t* x, const uint8_t* xs, const int32_t* 
 
 hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t* offsets, int64_t R,
                           int E, int H, int F, const float* wg, const float* wu, const float* wd,
-                          float* y_perm, float* h, hipStream_t s);
+                          float* y_perm, float* h, int num_cu, hipStream_t s);
 
 // One GEMM of the grouped FFN for small expert groups, K wide with N outputs per row: the
 // weights streamed through a ring of LDS stages; no tile prefix, no scratch.

@@ -53,14 +53,20 @@ def make(counts, H, F, dt, seed):
 
 @pytest.mark.parametrize("counts", list(COUNTS))
 @pytest.mark.parametrize("H,F", [(64, 64), (192, 320), (576, 64), (64, 448)])
-def test_f32_groups(counts, H, F):
+@pytest.mark.parametrize("tiles", ["by_size", "64x64"])
+def test_f32_groups(counts, H, F, tiles):
+    """A budget of two compute units leaves all but the smallest grids to the 64 x 64 tiles."""
     c = COUNTS[counts]
-    log(f"[gpu] f32 groups {counts} H={H} F={F}")
+    log(f"[gpu] f32 groups {counts} H={H} F={F} {tiles}")
     x, w, tok, off = make(c, H, F, torch.float32, 5)
     dx, dw, dtok, doff = x.cuda(), [t.cuda() for t in w], tok.cuda(), off.cuda()
-    y = moe.moe_grouped_ffn_gather(dx, dtok, doff, *dw)
-    y2 = moe.moe_grouped_ffn(dx[dtok.long()].contiguous(), doff, *dw)
-    torch.cuda.synchronize()
+    moe.set_cu_budget(2 if tiles == "64x64" else 0)
+    try:
+        y = moe.moe_grouped_ffn_gather(dx, dtok, doff, *dw)
+        y2 = moe.moe_grouped_ffn(dx[dtok.long()].contiguous(), doff, *dw)
+        torch.cuda.synchronize()
+    finally:
+        moe.set_cu_budget(0)
     assert torch.equal(y, y2)
     y = y.cpu().double()
     for e in range(len(c)):
