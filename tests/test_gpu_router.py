@@ -58,11 +58,9 @@ def check_outputs(x, w, k, renorm, lg, ids, wt, exact_ties=False):
     return safe.mean()
 
 
-# With H % 128 != 0 the per-wavefront kernel runs: T >= 65536 and >= 131072 give a
-# wavefront 32 and 64 tokens (on 256 compute units).  H % 128 == 0 with T >= 16384
-# runs the LDS-staged kernel (k-slices of 256 where H % 256 == 0, else of 128): 1
-# to 4 expert blocks, 4, 8 and 16 selection slots, ragged last block of 64 tokens;
-# below 16384 tokens the split-k kernel.
+# 1 to 4 expert blocks, 4, 8 and 16 selection slots; batches of the split-k kernel (H % 128 = 0
+# and up to 4096, 8192 or 12288 tokens by E, on 256 compute units), of two and of four
+# wavefronts per block, ragged last blocks.
 @pytest.mark.parametrize("T,E,k,H", [(1000, 8, 2, 256), (333, 64, 8, 448), (77, 3, 3, 64), (500, 40, 6, 4096),
                                      (129, 16, 4, 192), (257, 33, 16, 320), (5, 64, 1, 128),
                                      (70001, 20, 3, 64), (140007, 64, 4, 192), (40003, 64, 4, 128),
@@ -106,12 +104,9 @@ def test_router_workload(name):
 def test_router_batch_size_invariant(H, sizes):
     """The same tokens routed in batches of different sizes get bitwise-identical
     logits, ids and weights: every kernel variant (k split four ways for small
-    batches, LDS-staged router matrix, 16 / 32 / 64 tokens per wavefront) adds the
-    products in the same k order.  A budget of 4 compute units puts the variants'
-    switch points at small T: with H = 640 the sizes run split-k, then the
-    LDS-staged kernel with k-slices of 128; with H = 1024 split-k, then the
-    LDS-staged kernel with slices of 256; H = 192 (H % 128 != 0) runs one k chain in
-    the per-wavefront kernel at 16, 16, 32 and 64 tokens per wavefront."""
+    batches, two or four wavefronts per block) adds the products in the same k order.
+    A budget of 4 compute units puts the variants' switch points at 64 and 128 tokens
+    (64 experts); H = 192 (H % 128 != 0) runs one k chain."""
     rng = np.random.default_rng(H)
     E, k = 64, 4
     x = moegen.round_bf16(rng.standard_normal((max(sizes), H)).astype(np.float32))
@@ -148,3 +143,26 @@ def test_router_fullsize_memconstrained():
     frac = check_outputs(I.x[rows], w, c.k, 1, lg[rows], ids[rows], wt[rows])
     log(f"[gpu]   {frac:.4f} of the sampled tokens checked against the exact logits' routing")
     assert frac > 0.9
+
+
+@pytest.mark.parametrize("H", [64, 128, 192, 320, 384, 640])
+@pytest.mark.parametrize("E", [5, 16, 31, 48, 64])
+def test_router_switch_points(E, H):
+    """Batches on both sides of every switch between the kernels (a budget of 4 compute units
+    puts them at 64, 128 and 192 tokens, by E) and of the 16-token blocks, with H down to one
+    step of each kernel's k loop and quarters of odd length: each against the exact
+    logits, and all with the same bits for the tokens that they share."""
+    rng = np.random.default_rng(H + E)
+    sizes, k = (1, 15, 17, 63, 64, 65, 127, 128, 129, 192, 193, 259), min(E, 6)
+    x = moegen.round_bf16(rng.standard_normal((max(sizes), H)).astype(np.float32))
+    w = moegen.round_bf16((rng.standard_normal((E, H)) * H ** -0.5).astype(np.float32))
+    log(f"[gpu] router switch points E={E} H={H}")
+    moe.set_cu_budget(4)
+    try:
+        check(x, w, k)
+        full = run(x, w, k)
+        for T in sizes:
+            for a, b in zip(run(x[:T], w, k), full):
+                assert np.array_equal(a, b[:T]), T
+    finally:
+        moe.set_cu_budget(0)
