@@ -179,7 +179,8 @@ moe_status moe_permute_static(const int32_t* topk_ids, const void* x, int64_t T,
  * silu(z) = z / (1 + exp(-z)).  bf16: fp32 accumulation, h and y_perm rounded
  * to bf16 (nearest even).  f32: fp32 throughout.  Group sizes are read on the
  * device only (no host readback).  Results are deterministic for a given device
- * and compute-unit budget (moe_set_cu_budget): when the last round of
+ * and compute-unit budget (moe_set_cu_budget): R, E and the budget choose the
+ * kernel, and (large groups) when the last round of
  * down-projection tiles would leave the grid mostly idle, those tiles are
  * computed in pieces along k and their fp32 partial sums added in piece order,
  * so their rounding depends on the grid size.
@@ -350,13 +351,16 @@ moe_status moe_profiler_record(int i, const char** name, float* ms);
  * moe_set_cu_budget - compute units the library plans its persistent grids for
  * (a scheduling knob, not part of the layer).
  *
- * The grouped GEMMs, route, the fused router and the MXFP8 quantizer launch one
- * workgroup per compute unit (or a multiple of that) and share out their work
- * among them.  With n > 0 they plan for n compute units instead of the
+ * The bf16 and MXFP8 grouped GEMMs for large groups, route and the MXFP8 quantizer
+ * launch one workgroup per compute unit (or a multiple of that) and share out their
+ * work among them.  With n > 0 they plan for n compute units instead of the
  * device's count (values above the device's count are used as given), so a
- * caller can leave compute units to concurrent streams.  n = 0 restores the
- * device's count.  Results do not depend on it beyond fp32 rounding: how the
- * down projection's last round of tiles is split along k depends on the grid.
+ * caller can leave compute units to concurrent streams; the grouped GEMMs then run
+ * these kernels for small groups too, where a kernel with one workgroup per tile is
+ * otherwise faster.  The fp32 GEMMs and the fused router choose their tiles by it.
+ * n = 0 restores the device's count.  Results do not depend on it beyond fp32
+ * rounding: the order of the GEMMs' sums depends on the kernel, and how the down
+ * projection's last round of tiles is split along k on the grid.
  * Process-wide; set it between calls, not while other host threads launch.
  * Errors: INVALID_ARGUMENT for n < 0.
  */

@@ -467,6 +467,7 @@ void launch_gemm(const char* name, const StreamArgs& a, int num_cu, hipStream_t 
 // H 7168, 2048 rows, gate/up, 112 tiles: 118 (166); but 16 experts of H 2048, F 1408 at 250
 // rows, 176 tiles: 85 (71).
 bool use_stream_gemm(int64_t R, int E, int N, bool swiglu, bool fp8, int num_cu) {
+  if (cu_budget_set()) return false;      // the caller leaves compute units to other streams
   const Load l(R, E);
   if (l.rows <= (fp8 ? 96 : 112)) return true;
   const int cols = swiglu ? kTileCols / 2 : kTileCols;

@@ -59,6 +59,10 @@ hipStream_t stream_of(moe_stream s) { return reinterpret_cast<hipStream_t>(s); }
 
 }  // namespace
 
+namespace moe {
+bool cu_budget_set() { return g_cu_budget.load(std::memory_order_relaxed) > 0; }
+}  // namespace moe
+
 extern "C" {
 
 int moe_abi_version(void) { return MOE_ABI_VERSION; }

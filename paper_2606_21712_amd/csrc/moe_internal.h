@@ -75,8 +75,10 @@ hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t
 
 // One GEMM of the grouped FFN for small expert groups, K wide with N outputs per row: the
 // weights streamed through a ring of LDS stages; no tile prefix, no scratch.
-// use_stream_gemm: whether it is the faster one.  bf16: w1 != null is GEMM-1 (gate, up),
+// use_stream_gemm: whether it is the faster one; never under a compute-unit budget
+// (cu_budget_set), which only the persistent kernels hold to.  bf16: w1 != null is GEMM-1 (gate, up),
 // else GEMM-2; gather as launch_ffn_bf16, act_rows the rows of act.
+bool cu_budget_set();
 bool use_stream_gemm(int64_t R, int E, int N, bool swiglu, bool fp8, int num_cu);
 hipError_t launch_stream_gemm_bf16(const uint16_t* act, const int32_t* gather, int64_t act_rows, const int32_t* offsets,
                                    int64_t R, int E, int K, int N, const uint16_t* w0, const uint16_t* w1,

@@ -140,6 +140,34 @@ def test_large_kernel_edges(dtype):
         moe.set_cu_budget(0)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "mxfp8"])
+def test_budget_keeps_persistent_kernels(dtype):
+    """Under a compute-unit budget small groups, too, run on the kernels whose grids hold to it
+    (they find their tiles through a prefix launch; the streaming kernels have none)."""
+    x, w, tok, off = make([5, 9], 128, 128, torch.bfloat16, 3)
+    dx, dtok, doff = x.cuda(), tok.cuda(), off.cuda()
+    if dtype == "bf16":
+        dw = [t.cuda() for t in w]
+        call = lambda: moe.moe_grouped_ffn_gather(dx, dtok, doff, *dw)
+    else:
+        dw = [moe.quantize_weights_mxfp8(t.cuda()) for t in w]
+        xq = moe.moe_quantize_mxfp8(dx)
+        call = lambda: moe.moe_grouped_ffn_mxfp8_gather(xq, dtok, doff, *dw)
+    for budget, prefix in ((0, False), (8, True)):
+        log(f"[gpu] {dtype} small groups, budget {budget}")
+        moe.set_cu_budget(budget)
+        try:
+            call()
+            moe.profiler_start(16)
+            call()
+            torch.cuda.synchronize()
+            moe.profiler_stop()
+            names = [n for n, _ in moe.profiler_records()]
+        finally:
+            moe.set_cu_budget(0)
+        assert any("prefix" in n for n in names) == prefix, names
+
+
 def check_mxfp8(name, c, H, F):
     """The reference is dequantized in float64; the MFMA's fp8 sums are within 2^-12 of the sum
     of the products' magnitudes, and a code of h that rounds the other way moves it by at most
