@@ -298,7 +298,9 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
     if (S == 4 && it + 2 < steps) step(st2, st1, it + 2);
   };
   issue(st0, 0);
+  __builtin_amdgcn_sched_barrier(0);                 // the waits count on this order
   issue(st1, 1);
+  __builtin_amdgcn_sched_barrier(0);
   if constexpr (S == 4) issue(st2, 2);
   if (nbw == 0) kloop(std::integral_constant<int, 0>{});
   else if (NB >= 3 && nbw == 3) kloop(std::integral_constant<int, (NB >= 3 ? 3 : 1)>{});
