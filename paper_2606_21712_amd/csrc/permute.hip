@@ -19,6 +19,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "launch_rules.h"
 #include "moe_internal.h"
 
 namespace moe {
@@ -197,36 +198,38 @@ __global__ __launch_bounds__(kThreads) void permute_rank_kernel(
 
 // Small batches (at most kSmallUnits units): the three phases in one block of
 // 1024 threads.  Latency bounds it (dependent LDS reads and ballots), so the
-// assignments are dealt evenly over the 16 wavefronts in whole groups of 64, `iters` of
+// assignments are dealt evenly over the 16 wavefronts in whole groups of 64, ITERS of
 // them each, instead of filling one wavefront's 16 first; per-wavefront counts in
 // LDS.  Same results as count + rank.  Measured, 48 and 768 assignments over 8 and 64
-// experts: 11.1 -> 5.0 and 14.9 -> 5.0 us.
+// experts: 11.1 -> 5.0 and 14.9 -> 5.0 us.  ITERS is a constant, so that the groups' ballots
+// and LDS reads overlap: with a bound read at run time the loops end on a branch each round,
+// and 16384 assignments took 18.9 us instead of 15.9 (8 experts; 256: 27.2, 24.1).
 constexpr int kSmallUnits = 16;
 constexpr int kSmallThreads = kSmallUnits * kWave;
 
+template <int ITERS>
 __global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
-    const int32_t* __restrict__ ids, int64_t R, int E, int k, int nbits, int iters, int32_t* __restrict__ counts,
+    const int32_t* __restrict__ ids, int64_t R, int E, int k, int nbits, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ dest, int32_t* __restrict__ sorted_tok) {
   __shared__ int32_t run[kSmallUnits][kMaxExperts];
   __shared__ int32_t s_wsum[4];
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int w = tid / kWave;                                // the wavefront's share
-  const int64_t base = int64_t(w) * (iters * kWave);
+  const int64_t base = int64_t(w) * (ITERS * kWave);
   const uint64_t below = (1ull << lane) - 1ull;
   // its ids, all loaded at once and kept for the rank phase
-  int idv[kIters];
+  int idv[ITERS];
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) {
+  for (int it = 0; it < ITERS; ++it) {
     const int64_t a = base + it * kWave + lane;
-    idv[it] = it < iters && a < R ? ids[a] : -1;
+    idv[it] = a < R ? ids[a] : -1;
   }
   for (int e = lane; e < E; e += kWave) run[w][e] = 0;
   __syncthreads();
   // counts per share
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) {
-    if (it >= iters || base + it * kWave >= R) break;       // uniform across the wave
+  for (int it = 0; it < ITERS; ++it) {
     const bool valid = idv[it] >= 0;
     const int id = valid ? idv[it] : 0;
     const uint64_t match = wave_match(id, valid, nbits);
@@ -272,8 +275,7 @@ __global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
   __syncthreads();
   // rows: the share's running position per expert plus the rank among equal ids
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) {
-    if (it >= iters || base + it * kWave >= R) break;
+  for (int it = 0; it < ITERS; ++it) {
     const int64_t a = base + it * kWave + lane;
     const bool valid = idv[it] >= 0;
     const int id = valid ? idv[it] : 0;
@@ -321,6 +323,13 @@ __global__ __launch_bounds__(kThreads) void permute_copy_kernel(const uint8_t* _
   }
 }
 
+template <int ITERS>
+void launch_permute_small(const int32_t* ids, int64_t R, int E, int k, int nbits, int32_t* counts, int32_t* offsets,
+                          int32_t* dest, int32_t* sorted_tok, hipStream_t s) {
+  MOE_LAUNCH("permute_small", permute_small_kernel<ITERS>, dim3(1), dim3(kSmallThreads), s, ids, R, E, k, nbits,
+             counts, offsets, dest, sorted_tok);
+}
+
 }  // namespace
 
 hipError_t launch_permute(const int32_t* ids, const void* x, int64_t T, int E, int k, int H, int elt,
@@ -331,9 +340,15 @@ hipError_t launch_permute(const int32_t* ids, const void* x, int64_t T, int E, i
   int nbits = 0;
   while ((1 << nbits) < E) ++nbits;
   if (U <= kSmallUnits) {
-    const int iters = int((R + kSmallThreads - 1) / kSmallThreads);    // <= kIters
-    MOE_LAUNCH("permute_small", permute_small_kernel, dim3(1), dim3(kSmallThreads), s, ids, R, E, k, nbits, iters,
-               counts, offsets, dest, sorted_tok);
+    switch (permute_small_iters(R)) {
+      case 1: launch_permute_small<1>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s); break;
+      case 2: launch_permute_small<2>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s); break;
+      case 4: launch_permute_small<4>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s); break;
+      case 6: launch_permute_small<6>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s); break;
+      case 8: launch_permute_small<8>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s); break;
+      case 12: launch_permute_small<12>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s); break;
+      default: launch_permute_small<kIters>(ids, R, E, k, nbits, counts, offsets, dest, sorted_tok, s);
+    }
   } else {
     // per-block totals [E][Bpad] in the workspace (E * Bpad <= E * Upad ints)
     const int64_t B = Upad / kWavesPerBlock;

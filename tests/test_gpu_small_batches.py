@@ -15,9 +15,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,k,E", [(1, 1, 1), (63, 1, 3), (64, 1, 256), (65, 1, 7), (21, 3, 5), (512, 2, 64),
                                    (513, 2, 64), (1023, 1, 2), (341, 3, 8), (1025, 1, 256), (8191, 2, 9),
-                                   (8192, 2, 64), (1024, 16, 17), (1025, 16, 256)])
+                                   (8192, 2, 64), (1024, 16, 17), (1025, 16, 256),
+                                   (2049, 1, 5), (4097, 1, 256), (3072, 2, 8), (6145, 1, 31), (2049, 4, 64),
+                                   (6144, 2, 8), (12289, 1, 3)])
 def test_permute_small(T, k, E):
-    """Exactly the oracle's maps, below, at and above the single-block limit of 16384."""
+    """Exactly the oracle's maps, below, at and above the single-block limit of 16384 and the
+    sizes at which its wavefronts take one, 2, 4, 6, 8 and 12 groups of 64."""
     log(f"[gpu] permute maps T={T} k={k} E={E}")
     rng = np.random.default_rng(T * 31 + E)
     ids = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
