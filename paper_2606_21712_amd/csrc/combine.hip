@@ -9,6 +9,7 @@
 // Every output element is written by exactly one lane, so there are no atomics
 // and the result is deterministic.
 #include "common.h"
+#include "launch_rules.h"
 #include "moe_internal.h"
 
 namespace moe {
@@ -153,27 +154,26 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(const uint8_t* __rest
 template <bool BF16>
 void launch_combine_t(const uint8_t* yp, const int32_t* dest, const float* w, const uint8_t* ys, int64_t T,
                       int k, int64_t row_bytes, int splits, uint8_t* yo, unsigned blocks, hipStream_t s) {
-  // 32 (k = 1, 2: 8 or 16) sixteen-byte loads in flight per lane: k rows x UNROLL vectors.
   switch (k) {
     case 1:
-      MOE_LAUNCH("combine", (combine_kernel<BF16, 1, 8>), dim3(blocks), dim3(kThreads), s, yp, dest, w, ys, T,
-                 k, row_bytes, splits, yo);
+      MOE_LAUNCH("combine", (combine_kernel<BF16, 1, combine_unroll(1)>), dim3(blocks), dim3(kThreads), s,
+                 yp, dest, w, ys, T, k, row_bytes, splits, yo);
       break;
     case 2:
-      MOE_LAUNCH("combine", (combine_kernel<BF16, 2, 8>), dim3(blocks), dim3(kThreads), s, yp, dest, w, ys, T,
-                 k, row_bytes, splits, yo);
+      MOE_LAUNCH("combine", (combine_kernel<BF16, 2, combine_unroll(2)>), dim3(blocks), dim3(kThreads), s,
+                 yp, dest, w, ys, T, k, row_bytes, splits, yo);
       break;
     case 4:
-      MOE_LAUNCH("combine", (combine_kernel<BF16, 4, 8>), dim3(blocks), dim3(kThreads), s, yp, dest, w, ys, T,
-                 k, row_bytes, splits, yo);
+      MOE_LAUNCH("combine", (combine_kernel<BF16, 4, combine_unroll(4)>), dim3(blocks), dim3(kThreads), s,
+                 yp, dest, w, ys, T, k, row_bytes, splits, yo);
       break;
     case 8:
-      MOE_LAUNCH("combine", (combine_kernel<BF16, 8, 2>), dim3(blocks), dim3(kThreads), s, yp, dest, w, ys, T,
-                 k, row_bytes, splits, yo);
+      MOE_LAUNCH("combine", (combine_kernel<BF16, 8, combine_unroll(8)>), dim3(blocks), dim3(kThreads), s,
+                 yp, dest, w, ys, T, k, row_bytes, splits, yo);
       break;
     default:
-      MOE_LAUNCH("combine", (combine_kernel<BF16, 0, 2>), dim3(blocks), dim3(kThreads), s, yp, dest, w, ys, T,
-                 k, row_bytes, splits, yo);
+      MOE_LAUNCH("combine", (combine_kernel<BF16, 0, combine_unroll(0)>), dim3(blocks), dim3(kThreads), s,
+                 yp, dest, w, ys, T, k, row_bytes, splits, yo);
   }
 }
 
@@ -183,20 +183,7 @@ hipError_t launch_combine(const void* y_perm, const int32_t* dest, const float* 
                           int64_t T, int k, int H, bool bf16, void* y, hipStream_t s) {
   const int64_t row_bytes = int64_t(H) * (bf16 ? 2 : 4);
   const int nvec = int(row_bytes / 16);
-  // Column split: a token's row is cut into `splits` parts, one wavefront each, so
-  // that large batches run enough wavefronts with a few vectors per lane each
-  // (measured cold, % of 8 TB/s: memory-constrained 71 -> 76 with 2 parts,
-  // Mixtral-shaped 32K tokens 75 -> 77 with 4, DeepSeek-shaped 65 -> 70 with 8).
-  // Up to 4096 wavefronts the latency of a row bounds it: as many parts as leave each
-  // lane a vector (96 tokens, k 8, H 7168: 18.1 -> 5.8 us).
-  // Batches between (4096 to 8192 tokens) keep whole rows.
-  int splits = 1;
-  if (T < 4096)
-    while (splits < 16 && nvec / (2 * splits) >= kWave && T * (2 * splits) <= 4096) splits *= 2;
-  else if (T >= 8192)
-    while (splits < 8 && nvec / (2 * splits) >= kWave && T * splits < (int64_t(1) << 30) &&
-           (nvec / splits > 4 * kWave || T * splits < 131072))
-      splits *= 2;
+  const int splits = combine_splits(T, k, nvec);
   const unsigned blocks = unsigned((T * splits + kWavesPerBlock - 1) / kWavesPerBlock);
   auto yp = static_cast<const uint8_t*>(y_perm);
   auto ys = static_cast<const uint8_t*>(y_shared);

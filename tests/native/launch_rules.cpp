@@ -12,6 +12,11 @@ int main() {
       int64_t R;
       std::cin >> R;
       std::cout << moe::permute_small_iters(R) << "\n";
+    } else if (rule == "combine") {
+      int64_t T;
+      int k, nvec;
+      std::cin >> T >> k >> nvec;
+      std::cout << moe::combine_splits(T, k, nvec) << "\n";
     } else {
       return 1;
     }

@@ -33,3 +33,22 @@ def test_permute_groups(rules):
     for R, n in zip(sizes, map(int, rules([f"permute {R}" for R in sizes]))):
         assert n <= 16 and n * 1024 >= R, (R, n)
         assert R <= 4096 or n * 1024 < 1.5 * R + 1024, (R, n)
+
+
+def test_combine_splits(rules):
+    """Every lane of a part has a vector; parts only where they were measured faster: not for
+    rows of one pass (8 vectors per lane with k = 1, 2, 4) from 640 tokens, and up to 4096
+    wavefronts for rows of several."""
+    cases = [(T, k, H * 2 // 16) for T in (1, 96, 509, 640, 1024, 2048, 2049, 4095, 4096, 8191, 8192, 131072)
+             for k in (1, 2, 3, 4, 8, 16) for H in (64, 1024, 2048, 4096, 7168, 16384)]
+    for (T, k, nvec), s in zip(cases, map(int, rules(["combine %d %d %d" % c for c in cases]))):
+        assert s in (1, 2, 4, 8, 16) and (s == 1 or nvec // s >= 64), (T, k, nvec, s)
+        one_pass = nvec <= 64 * (8 if k in (1, 2, 4) else 2)
+        if T < 4096:
+            assert s == 1 or T * s <= (2800 if one_pass else 4096), (T, k, nvec, s)
+            assert s == 1 or not one_pass or T < 640, (T, k, nvec, s)
+        elif T < 8192:
+            assert s == 1
+    got = rules(["combine 96 8 896", "combine 509 4 512", "combine 2048 2 512", "combine 2048 8 896",
+                 "combine 131072 4 512"])
+    assert got == ["8", "4", "1", "2", "2"]
