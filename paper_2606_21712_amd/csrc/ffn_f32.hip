@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kFThreads, 4) void grouped_gemm_f32_kernel(GemmArgs
     st1[tid] = 0;
   }
   MTile tile;
-  if (!locate_tile<kFM>(p.offsets, p.E, p.ntiles, int(blockIdx.x), &tile)) return;     // uniform across the block
+  if (!locate_tile<kFM>(p.offsets, p.E, p.ntiles, tile_workgroup(), &tile)) return;     // uniform across the block
   const int e = tile.e, nt = tile.nt, row0 = tile.row0, row_stop = tile.row_stop;
   const int K = p.K, N = p.N;
   const int n0 = nt * (SWIGLU ? kFN / 2 : kFN);
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kFThreads, 2) void grouped_gemm_f32_small_kernel(Ge
     st1[tid] = 0;
   }
   MTile tile;
-  if (!locate_tile<32>(p.offsets, p.E, p.ntiles, int(blockIdx.x), &tile)) return;      // uniform across the block
+  if (!locate_tile<32>(p.offsets, p.E, p.ntiles, tile_workgroup(), &tile)) return;      // uniform across the block
   const int e = tile.e, row0 = tile.row0, row_stop = tile.row_stop;
   const int K = p.K, N = p.N;
   const int n0 = tile.nt * (SWIGLU ? 16 : 32);
@@ -278,11 +278,11 @@ void launch_gemm_f32(const char* name, GemmArgsF a, int64_t R, int num_cu, hipSt
   const int64_t small = (R + live * 31) / 32 * (a.N / (SWIGLU ? 16 : 32));
   if (small <= 2 * num_cu) {
     a.ntiles = a.N / (SWIGLU ? 16 : 32);
-    MOE_LAUNCH(name, grouped_gemm_f32_small_kernel<SWIGLU>, dim3(tile_grid(small)), dim3(kFThreads), s, a);
+    MOE_LAUNCH(name, grouped_gemm_f32_small_kernel<SWIGLU>, tile_dim(small), dim3(kFThreads), s, a);
   } else {
     a.ntiles = a.N / (SWIGLU ? kFN / 2 : kFN);
     const int64_t mtiles = (R + live * (kFM - 1)) / kFM;
-    MOE_LAUNCH(name, grouped_gemm_f32_kernel<SWIGLU>, dim3(tile_grid(mtiles * a.ntiles)), dim3(kFThreads), s, a);
+    MOE_LAUNCH(name, grouped_gemm_f32_kernel<SWIGLU>, tile_dim(mtiles * a.ntiles), dim3(kFThreads), s, a);
   }
 }
 

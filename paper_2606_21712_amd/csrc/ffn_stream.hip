@@ -102,7 +102,7 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
     if (S == 4) st3[tid & 15] = 0;
   }
   MTile tile;
-  if (!locate_tile<MR>(p.offsets, p.E, p.ntiles, int(blockIdx.x), &tile)) return;     // uniform across the block
+  if (!locate_tile<MR>(p.offsets, p.E, p.ntiles, tile_workgroup(), &tile)) return;     // uniform across the block
   const int e = tile.e, nt = tile.nt, row0 = tile.row0, row_stop = tile.row_stop;
   const int K = p.K, N = p.N;
   const int n0 = nt * kCols;
@@ -405,7 +405,7 @@ void launch_tiles(const char* name, StreamArgs a, hipStream_t s) {
   a.ntiles = (a.N + cols - 1) / cols;
   const int64_t mtiles = (int64_t(a.R) + int64_t(std::min(a.E, a.R)) * (MR - 1)) / MR;
   const int64_t weight_bytes = int64_t(a.E) * a.N * a.K * (FP8 ? 1 : 2) * (SWIGLU ? 2 : 1);
-  const dim3 grid(tile_grid(mtiles * a.ntiles)), block(128 * WN * KG);
+  const dim3 grid = tile_dim(mtiles * a.ntiles), block(128 * WN * KG);
   if (weight_bytes >= (int64_t(128) << 20) && Load(a.R, a.E).rows <= MR)
     MOE_LAUNCH(name, (stream_gemm_kernel<FP8, SWIGLU, WN, MR, KG, S, true>), grid, block, s, a);
   else

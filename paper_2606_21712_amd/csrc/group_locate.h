@@ -2,6 +2,7 @@
 // that writes a tile prefix first.
 #pragma once
 #include "common.h"
+#include "launch_rules.h"
 
 namespace moe {
 
@@ -11,6 +12,15 @@ struct MTile {
   int row0;       // first grouped row of the tile
   int row_stop;   // end of the tile's rows
 };
+
+inline dim3 tile_dim(int64_t tiles) {
+  const TileGrid g = tile_grid(tiles);
+  return dim3(g.x, g.y);
+}
+
+// Number of this workgroup in a tile_grid() launch.  (gridDim.x in the constant's place would be
+// read from memory, and cost the smallest fp32 layer 3%.)
+__device__ __forceinline__ int tile_workgroup() { return int(blockIdx.y * kTileGridX + blockIdx.x); }
 
 // The tile of workgroup b, false when it has none.  Expert e has ceil(rows / BM) m-tiles,
 // its 32-row blocks shared out evenly among them (BM % 32 = 0, so none exceeds BM rows),
@@ -69,8 +79,5 @@ __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets,
   }
   return false;
 }
-
-// Workgroups that cover `tiles` tiles in eight parts.
-inline unsigned tile_grid(int64_t tiles) { return unsigned((tiles + kNumXcd - 1) / kNumXcd * kNumXcd); }
 
 }  // namespace moe

@@ -5,6 +5,20 @@
 
 namespace moe {
 
+// Grid of the kernels with one workgroup per tile: at least `tiles` workgroups, numbered
+// y * kTileGridX + x, in eight parts (number n runs on XCD n % 8).  Two dimensions once one
+// would pass the launch's limit of 2^32 threads along it (workgroups have at most 512): fp32
+// gate/up tiles of a workspace of 137 GB are 2^24.
+struct TileGrid {
+  unsigned x, y;
+};
+constexpr unsigned kTileGridX = 1u << 22;
+inline TileGrid tile_grid(int64_t tiles) {
+  const int64_t n = (tiles + 7) / 8 * 8;
+  if (n <= kTileGridX) return TileGrid{unsigned(n), 1};
+  return TileGrid{kTileGridX, unsigned((n + kTileGridX - 1) / kTileGridX)};
+}
+
 // One-block permute (up to 16384 assignments): groups of 64 that each of its 16 wavefronts
 // takes, a constant of the kernel: the next built size up.  Sizes 6 and 12 because a third
 // of the groups empty shows: 8200 assignments over 256 experts take 21.1 us in 16 groups,

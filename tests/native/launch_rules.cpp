@@ -17,6 +17,11 @@ int main() {
       int k, nvec;
       std::cin >> T >> k >> nvec;
       std::cout << moe::combine_splits(T, k, nvec) << "\n";
+    } else if (rule == "grid") {
+      int64_t tiles;
+      std::cin >> tiles;
+      const moe::TileGrid g = moe::tile_grid(tiles);
+      std::cout << g.x << " " << g.y << "\n";
     } else {
       return 1;
     }

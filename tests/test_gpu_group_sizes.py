@@ -219,3 +219,40 @@ def quantize64(v):
     q = b / s
     step = torch.exp2((torch.frexp(q)[1].double() - 1.0).clamp_min(-6.0) - 3.0)
     return ((torch.round(q / step) * step).clamp(-448.0, 448.0) * s).reshape(v.shape)
+
+
+def test_f32_grid_past_2_32_threads():
+    """So many gate/up tiles (2^24 of 64 x 32, h of 137 GB) that one grid dimension would pass
+    2^32 threads.  Every row repeats one of 1024 tokens, so a call on those alone, checked
+    against float64, gives every row's bits (a budget of one compute unit leaves it, too, to
+    the 64 x 64 tiles: the same k order)."""
+    H, F, T, E, R = 64, 16384, 1024, 2, (1 << 21) + 100
+    if torch.cuda.mem_get_info()[0] < 150e9:
+        torch.cuda.empty_cache()
+        if torch.cuda.mem_get_info()[0] < 150e9:
+            pytest.skip("needs 150 GB of free device memory")
+    log(f"[gpu] f32 grid H={H} F={F} R={R}")
+    g = torch.Generator().manual_seed(3)
+    x = torch.randn(T, H, generator=g)
+    w = [torch.randn(E, F, H, generator=g) * H ** -0.5, torch.randn(E, F, H, generator=g) * H ** -0.5,
+         torch.randn(E, H, F, generator=g) * F ** -0.5]
+    dx, dw = x.cuda(), [t.cuda() for t in w]
+    tok = torch.arange(T, dtype=torch.int32, device="cuda")
+    moe.set_cu_budget(1)
+    try:
+        few = moe.moe_grouped_ffn_gather(dx, tok.repeat(E),
+                                         torch.tensor([0, T, 2 * T], dtype=torch.int32, device="cuda"), *dw)
+    finally:
+        moe.set_cu_budget(0)
+    many = (torch.arange(R, device="cuda") * 37 % T).to(torch.int32)
+    split = R // 3
+    ws = torch.empty(moe.moe_grouped_ffn_workspace_bytes(R, E, H, F, torch.float32), dtype=torch.uint8, device="cuda")
+    y = moe.moe_grouped_ffn_gather(dx, many, torch.tensor([0, split, R], dtype=torch.int32, device="cuda"), *dw, ws=ws)
+    torch.cuda.synchronize()
+    del ws
+    torch.cuda.empty_cache()
+    assert torch.equal(y[:split], few[many[:split].long()])
+    assert torch.equal(y[split:], few[T + many[split:].long()])
+    for e in range(E):
+        ref, bound = ffn_bound(x[:16].double(), *(t[e].double() for t in w), 0.0, 2.0 ** -24)
+        assert ((few[e * T:e * T + 16].cpu().double() - ref).abs() <= bound).all()

@@ -52,3 +52,14 @@ def test_combine_splits(rules):
     got = rules(["combine 96 8 896", "combine 509 4 512", "combine 2048 2 512", "combine 2048 8 896",
                  "combine 131072 4 512"])
     assert got == ["8", "4", "1", "2", "2"]
+
+
+def test_tile_grid(rules):
+    """Every tile has a workgroup, in launches that the runtime takes (under 2^32 threads along
+    a dimension with workgroups of 512, at most 65535 along y), up to R x F of 2^37 in fp32
+    gate/up tiles of 64 x 32."""
+    tiles = [1, 7, 8, 9, 1000, (1 << 22) - 1, 1 << 22, (1 << 22) + 1, (1 << 24) - 8, 1 << 24, (1 << 24) + 511, 1 << 26]
+    for n, out in zip(tiles, rules([f"grid {n}" for n in tiles])):
+        x, y = map(int, out.split())
+        assert x % 8 == 0 and x * y >= n and x * 512 < 1 << 32 and 1 <= y <= 65535, (n, x, y)
+        assert y > 1 or x < n + 8
