@@ -179,7 +179,7 @@ moe_status moe_permute_static(const int32_t* topk_ids, const void* x, int64_t T,
  * silu(z) = z / (1 + exp(-z)).  bf16: fp32 accumulation, h and y_perm rounded
  * to bf16 (nearest even).  f32: fp32 throughout.  Group sizes are read on the
  * device only (no host readback).  Results are deterministic for a given device
- * and compute-unit budget (moe_set_cu_budget): R, E and the budget choose the
+ * and compute-unit budget (moe_set_cu_budget): R, E, H, F and the budget choose the
  * kernel, and (large groups) when the last round of
  * down-projection tiles would leave the grid mostly idle, those tiles are
  * computed in pieces along k and their fp32 partial sums added in piece order,

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) void tile_prefix_kernel(const int32_t* __restr
                                                          int bm, int32_t* __restrict__ prefix,
                                                          int32_t* __restrict__ queues) {
   const int e = threadIdx.x;
-  if (queues != nullptr && e < kQueueInts) queues[e] = 0;      // tile queues of both GEMMs
+  if (e < kQueueInts) queues[e] = 0;      // tile queues of both GEMMs
   int32_t mt = 0;
   if (e < E) {
     const int32_t c = offsets[e + 1] - offsets[e];
@@ -567,8 +567,8 @@ hipError_t launch_ffn_bf16(const uint16_t* act, const int32_t* gather, int64_t T
                            int64_t R, int E, int H, int F, const uint16_t* wg, const uint16_t* wu,
                            const uint16_t* wd, uint16_t* y_perm, int32_t* mtile_prefix, int32_t* queues,
                            uint16_t* h, float* partial, int num_cu, hipStream_t s) {
-  const bool stream1 = use_stream_gemm(R, E, F, true, false, num_cu);
-  const bool stream2 = use_stream_gemm(R, E, H, false, false, num_cu);
+  const bool stream1 = use_stream_gemm(R, E, H, F, true, false, num_cu);
+  const bool stream2 = use_stream_gemm(R, E, F, H, false, false, num_cu);
   if (!stream1 || !stream2)
     MOE_LAUNCH("ffn_tile_prefix", tile_prefix_kernel, dim3(1), dim3(256), s, offsets, E, kBMMax, mtile_prefix, queues);
   const int64_t mtiles_upper = (R + int64_t(E) * (kBM - 1)) / kBM;

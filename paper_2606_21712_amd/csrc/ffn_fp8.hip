@@ -467,8 +467,8 @@ hipError_t launch_ffn_mxfp8(const uint8_t* x, const uint8_t* xs, const int32_t* 
                             const uint8_t* wgs, const uint8_t* wu, const uint8_t* wus, const uint8_t* wd,
                             const uint8_t* wds, uint16_t* y_perm, int32_t* mtile_prefix, int32_t* queues, uint8_t* h,
                             uint8_t* hs, float* partial, int num_cu, hipStream_t s) {
-  const bool stream1 = use_stream_gemm(R, E, F, true, true, num_cu);
-  const bool stream2 = use_stream_gemm(R, E, H, false, true, num_cu);
+  const bool stream1 = use_stream_gemm(R, E, H, F, true, true, num_cu);
+  const bool stream2 = use_stream_gemm(R, E, F, H, false, true, num_cu);
   hipError_t err = hipSuccess;
   if (!stream1 || !stream2) err = launch_tile_prefix(offsets, E, kBM, mtile_prefix, queues, s);
   if (err != hipSuccess) return err;

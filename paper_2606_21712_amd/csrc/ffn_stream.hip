@@ -30,7 +30,6 @@
 // The operands, their LDS layout and the MFMA instructions are those of the large-batch
 // kernels (ffn.hip, ffn_fp8.hip), with the weight tile as the MFMA A operand.
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "group_locate.h"
@@ -391,90 +390,40 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
   }
 }
 
-// Experts that R rows dealt evenly at random reach, and their average rows.
-struct Load {
-  double live;
-  int64_t rows;
-  Load(int64_t R, int E)
-      : live(E > 1 ? E * -std::expm1(double(R) * std::log1p(-1.0 / E)) : 1.0), rows(int64_t(double(R) / live + 0.999)) {}
-};
-
 template <bool FP8, bool SWIGLU, int WN, int MR, int KG, int S>
 void launch_tiles(const char* name, StreamArgs a, hipStream_t s) {
   const int cols = 64 * WN / (SWIGLU ? 2 : 1);
   a.ntiles = (a.N + cols - 1) / cols;
   const int64_t mtiles = (int64_t(a.R) + int64_t(std::min(a.E, a.R)) * (MR - 1)) / MR;
-  const int64_t weight_bytes = int64_t(a.E) * a.N * a.K * (FP8 ? 1 : 2) * (SWIGLU ? 2 : 1);
   const dim3 grid = tile_dim(mtiles * a.ntiles), block(128 * WN * KG);
-  if (weight_bytes >= (int64_t(128) << 20) && Load(a.R, a.E).rows <= MR)
+  if (stream_nt(a.R, a.E, a.K, a.N, SWIGLU, FP8, MR))
     MOE_LAUNCH(name, (stream_gemm_kernel<FP8, SWIGLU, WN, MR, KG, S, true>), grid, block, s, a);
   else
     MOE_LAUNCH(name, (stream_gemm_kernel<FP8, SWIGLU, WN, MR, KG, S, false>), grid, block, s, a);
 }
 
-// Workgroups of a launch with WN, MR at that load.
-template <bool SWIGLU>
-int64_t workgroups(const StreamArgs& a, const Load& l, int WN, int MR) {
-  const int cols = 64 * WN / (SWIGLU ? 2 : 1);
-  return int64_t(l.live * double((l.rows + MR - 1) / MR) * double((a.N + cols - 1) / cols));
-}
-
-// Which tile.  More activation rows per tile read the weights fewer times and the
-// activations less often, fewer give more workgroups; the lines lie where the mean group
-// leaves its largest members inside one tile (a group cut in two reads its weights from L2
-// twice).  Measured, us of one GEMM (M: H 4096, F 14336, 8 experts):
-//   160 rows for means of 100 to 320: M down at 256 rows 289 (128 rows: 430); beyond that
-//     128 rows (one expert, 2048 rows, H 7168, F 2048, gate/up: 114, 160 rows: 191);
-//   fewer workgroups than two per compute unit: two k groups, which keep as many bytes in
-//     flight on half the workgroups (M down at one row: 80 -> 52), and four on 64 weight
-//     rows when even that leaves half the chip idle (one expert, F 2048, H 7168 at 8 rows,
-//     gate/up: 31 -> 21).
 template <bool FP8, bool SWIGLU>
 void launch_gemm(const char* name, const StreamArgs& a, int num_cu, hipStream_t s) {
-  const Load l(a.R, a.E);
-  auto wg = [&](int WN, int MR) { return workgroups<SWIGLU>(a, l, WN, MR); };
-  if constexpr (!FP8) {          // (three stages of 160 rows and their scales exceed the LDS)
-    if (l.rows > 100 && l.rows <= 320) {
-      if (wg(4, 160) >= num_cu) return launch_tiles<FP8, SWIGLU, 4, 160, 1, 3>(name, a, s);
-      if (wg(2, 160) >= num_cu * 3 / 4) return launch_tiles<FP8, SWIGLU, 2, 160, 1, 4>(name, a, s);
-    }
+  const StreamTile t = stream_tile(a.R, a.E, a.N, SWIGLU, FP8, num_cu);
+  if constexpr (!FP8) {
+    if (t.mr == 160 && t.wn == 4) return launch_tiles<FP8, SWIGLU, 4, 160, 1, 3>(name, a, s);
+    if (t.mr == 160) return launch_tiles<FP8, SWIGLU, 2, 160, 1, 4>(name, a, s);
   }
-  if (l.rows > 44) {
-    if (wg(4, 128) >= num_cu) return launch_tiles<FP8, SWIGLU, 4, 128, 1, 3>(name, a, s);
-    if (wg(2, 128) >= num_cu * 3 / 4) return launch_tiles<FP8, SWIGLU, 2, 128, 1, 4>(name, a, s);
-  }
-  if (l.rows <= 16) {
-    if (wg(2, 32) >= 2 * num_cu) launch_tiles<FP8, SWIGLU, 2, 32, 1, 3>(name, a, s);
-    else if (wg(2, 32) >= num_cu / 2) launch_tiles<FP8, SWIGLU, 2, 32, 2, 3>(name, a, s);
-    else launch_tiles<FP8, SWIGLU, 1, 32, 4, 3>(name, a, s);
-  } else {
-    if (wg(2, 64) >= 2 * num_cu) launch_tiles<FP8, SWIGLU, 2, 64, 1, 3>(name, a, s);
-    else if (wg(2, 64) >= num_cu / 2) launch_tiles<FP8, SWIGLU, 2, 64, 2, 3>(name, a, s);
-    else launch_tiles<FP8, SWIGLU, 1, 64, 2, 4>(name, a, s);
-  }
+  if (t.mr == 128 && t.wn == 4) return launch_tiles<FP8, SWIGLU, 4, 128, 1, 3>(name, a, s);
+  if (t.mr == 128) return launch_tiles<FP8, SWIGLU, 2, 128, 1, 4>(name, a, s);
+  if (t.mr == 64 && t.wn == 1) return launch_tiles<FP8, SWIGLU, 1, 64, 2, 4>(name, a, s);
+  if (t.mr == 64 && t.kg == 2) return launch_tiles<FP8, SWIGLU, 2, 64, 2, 3>(name, a, s);
+  if (t.mr == 64) return launch_tiles<FP8, SWIGLU, 2, 64, 1, 3>(name, a, s);
+  if (t.wn == 1) return launch_tiles<FP8, SWIGLU, 1, 32, 4, 3>(name, a, s);
+  if (t.kg == 2) return launch_tiles<FP8, SWIGLU, 2, 32, 2, 3>(name, a, s);
+  launch_tiles<FP8, SWIGLU, 2, 32, 1, 3>(name, a, s);
 }
 
 }  // namespace
 
-// Against the large-batch kernels, us of the FFN, here (there).  M as above, D: H 7168,
-// F 2048, 64 experts; C: H 4096, F 4096, 64 experts.
-//   bf16: M at 6 rows 427 (660), 64 rows 484 (745), 127 rows 590 (804), 175 rows gate/up 532
-//   (522); D at 12 rows 838 (1005), 64 rows 943 (1061), 128 rows 1123 (1189); C at 16 rows 954
-//   (1091), 128 rows 1249 (1361), but 1500 (1440) when the loads are lognormal (sigma 1):
-//   uneven groups have more tiles than their mean says, so the line lies below that;
-//   MXFP8: D at 25 rows 471 (567), 100 rows 627 (632), 128 rows 721 (669); M at 6 rows 217
-//   (374), 64 rows 267 (392), 127 rows 413 (418).
-// Few tiles leave the large-batch kernels' grid part empty; there the line lies further out:
-// M bf16 at 127 rows, 896 tiles; M down at 256 rows, 128 tiles: 286 (386); one expert, F 2048,
-// H 7168, 2048 rows, gate/up, 112 tiles: 118 (166); but 16 experts of H 2048, F 1408 at 250
-// rows, 176 tiles: 85 (71).
-bool use_stream_gemm(int64_t R, int E, int N, bool swiglu, bool fp8, int num_cu) {
+bool use_stream_gemm(int64_t R, int E, int K, int N, bool swiglu, bool fp8, int num_cu) {
   if (cu_budget_set()) return false;      // the caller leaves compute units to other streams
-  const Load l(R, E);
-  if (l.rows <= (fp8 ? 96 : 112)) return true;
-  const int cols = swiglu ? kTileCols / 2 : kTileCols;
-  const int64_t big = int64_t(l.live * double((l.rows + kTileRowsMax - 1) / kTileRowsMax) * double((N + cols - 1) / cols));
-  return 2 * big <= num_cu || (!fp8 && l.rows <= 144 && big < 4 * num_cu);
+  return stream_is_faster(R, E, K, N, swiglu, fp8, num_cu);
 }
 
 hipError_t launch_stream_gemm_bf16(const uint16_t* act, const int32_t* gather, int64_t act_rows, const int32_t* offsets,

@@ -51,7 +51,7 @@ hipError_t launch_ffn_bf16(const uint16_t* act, const int32_t* gather, int64_t T
 hipError_t launch_tail_reduce(const float* partial, const int32_t* mtile_prefix, const int32_t* offsets, int E,
                               int NT, int G, int KT, int N, uint16_t* y, bool row_blocks, hipStream_t s);
 // Per-expert m-tile prefix of the device-side offsets (one block): ceil(rows /
-// bm) m-tiles per expert; zeroes the GEMMs' tile counters when queues != null.
+// bm) m-tiles per expert; zeroes the GEMMs' tile counters.
 hipError_t launch_tile_prefix(const int32_t* offsets, int E, int bm, int32_t* mtile_prefix, int32_t* queues,
                               hipStream_t s);
 
@@ -79,7 +79,7 @@ hipError_t launch_ffn_f32(const float* act, const int32_t* gather, const int32_t
 // (cu_budget_set), which only the persistent kernels hold to.  bf16: w1 != null is GEMM-1 (gate, up),
 // else GEMM-2; gather as launch_ffn_bf16, act_rows the rows of act.
 bool cu_budget_set();
-bool use_stream_gemm(int64_t R, int E, int N, bool swiglu, bool fp8, int num_cu);
+bool use_stream_gemm(int64_t R, int E, int K, int N, bool swiglu, bool fp8, int num_cu);
 hipError_t launch_stream_gemm_bf16(const uint16_t* act, const int32_t* gather, int64_t act_rows, const int32_t* offsets,
                                    int64_t R, int E, int K, int N, const uint16_t* w0, const uint16_t* w1,
                                    uint16_t* out, int num_cu, hipStream_t s);

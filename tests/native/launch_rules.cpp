@@ -22,6 +22,19 @@ int main() {
       std::cin >> tiles;
       const moe::TileGrid g = moe::tile_grid(tiles);
       std::cout << g.x << " " << g.y << "\n";
+    } else if (rule == "stream") {
+      // "0", or "wn mr kg stages nt" where the streaming kernels take the GEMM
+      int64_t R;
+      int E, K, N, num_cu;
+      bool swiglu, fp8;
+      std::cin >> R >> E >> K >> N >> swiglu >> fp8 >> num_cu;
+      if (!moe::stream_is_faster(R, E, K, N, swiglu, fp8, num_cu)) {
+        std::cout << "0\n";
+        continue;
+      }
+      const moe::StreamTile t = moe::stream_tile(R, E, N, swiglu, fp8, num_cu);
+      std::cout << t.wn << " " << t.mr << " " << t.kg << " " << t.stages << " "
+                << moe::stream_nt(R, E, K, N, swiglu, fp8, t.mr) << "\n";
     } else {
       return 1;
     }

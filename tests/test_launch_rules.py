@@ -63,3 +63,36 @@ def test_tile_grid(rules):
         x, y = map(int, out.split())
         assert x % 8 == 0 and x * y >= n and x * 512 < 1 << 32 and 1 <= y <= 65535, (n, x, y)
         assert y > 1 or x < n + 8
+
+
+def stream_choices(rules, c, H, F, fp8):
+    E, R = len(c), sum(c)
+    return rules([f"stream {R} {E} {H} {F} 1 {fp8} 256", f"stream {R} {E} {F} {H} 0 {fp8} 256"])
+
+
+# (mean rows, H, F, experts, MXFP8, GEMM, streams): both sides of the lines, where they were measured
+LINES = [
+    # the shapes of the repository's workloads
+    (3, 4096, 14336, 8, 0, "gate", 1), (128, 4096, 14336, 8, 0, "gate", 1), (160, 4096, 14336, 8, 0, "gate", 0),
+    (128, 4096, 14336, 8, 0, "down", 1), (220, 4096, 14336, 8, 0, "down", 1), (300, 4096, 14336, 8, 0, "down", 0),
+    (12, 7168, 2048, 64, 0, "gate", 1), (112, 7168, 2048, 64, 0, "gate", 1), (128, 7168, 2048, 64, 0, "gate", 0),
+    (80, 7168, 2048, 64, 0, "down", 1), (96, 7168, 2048, 64, 0, "down", 0),
+    (112, 4096, 4096, 64, 0, "down", 1), (128, 4096, 4096, 64, 0, "down", 0),
+    (96, 4096, 14336, 8, 1, "gate", 1), (128, 4096, 14336, 8, 1, "gate", 0),
+    (25, 7168, 2048, 64, 1, "down", 1), (96, 7168, 2048, 64, 1, "down", 0),
+    # MXFP8 tiles of the large-batch kernel are 256 rows: a grid that it fills, and ones that it does not
+    (256, 4096, 14336, 8, 1, "down", 1), (300, 4096, 14336, 8, 1, "down", 1), (330, 4096, 14336, 8, 1, "down", 0),
+    (400, 5120, 1536, 4, 1, "down", 1), (640, 4096, 14336, 4, 1, "down", 1), (500, 4096, 14336, 8, 1, "down", 0),
+    # bf16: few tiles, but more of the streaming kernel's than run at once
+    (400, 4096, 14336, 4, 0, "down", 1), (500, 4096, 14336, 4, 0, "down", 0), (640, 5120, 1536, 4, 0, "gate", 0),
+    # short k loops, and many rounds of large tiles
+    (40, 2048, 768, 128, 0, "down", 1), (52, 2048, 768, 128, 0, "down", 0), (24, 2048, 768, 128, 1, "down", 1),
+    (40, 2048, 768, 128, 1, "down", 0), (64, 2816, 1408, 60, 1, "down", 1), (96, 2816, 1408, 60, 1, "down", 0),
+    (24, 7168, 2048, 256, 0, "down", 1), (40, 7168, 2048, 256, 0, "down", 0),
+]
+
+
+@pytest.mark.parametrize("mean,H,F,E,fp8,gemm,streams", LINES)
+def test_stream_lines(rules, mean, H, F, E, fp8, gemm, streams):
+    got = stream_choices(rules, [mean] * E, H, F, fp8)[gemm == "down"]
+    assert (got != "0") == bool(streams), got
