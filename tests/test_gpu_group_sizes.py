@@ -77,8 +77,13 @@ def test_f32_groups(counts, H, F, tiles):
 
 
 # The streaming kernels pick tiles of 32, 64, 128 or 160 rows, one to four k groups and 64 to
-# 256 weight rows by the average group size and the number of tiles: (counts, H, F) that reach
-# each of them, with groups on and around the tile edges and F, H off the column tiles.
+# 256 weight rows by the average group size and the number of tiles, and bypass the caches
+# (nt) for weights of 128 MB and more: (counts, H, F), with groups on and around the tile edges
+# and F, H off the column tiles.  STREAM_TILES says which kernels each reaches.
+W32 = [1, 0, 16, 9, 31, 32, 33, 2]
+W64 = [63, 64, 65, 1, 0, 40, 20, 30]
+W128 = [127, 128, 129, 1, 0, 64, 32, 33]
+W160 = [159, 160, 161, 95, 96, 97, 129, 128]
 STREAM = {
     "decode_few": ([0, 1, 3, 0, 32, 33, 1], 192, 320),
     "decode_k_groups": ([2, 1, 0, 5], 4160, 64),
@@ -91,7 +96,88 @@ STREAM = {
     "mid160": ([159, 160, 161, 95, 96, 97, 129, 128], 4160, 4160),
     "mid160_half": ([159, 160, 161, 320, 321, 1, 100, 128], 3136, 1664),
     "one_expert": ([577], 448, 320),
+    "w32": (W32 * 8, 1152, 1088),
+    "w32_gate": (W32 * 8, 192, 576),
+    "w32_down": (W32 * 8, 1152, 64),
+    "w32_k2": (W32 * 2, 2304, 1984),
+    "w32_k2_small": (W32 * 8, 320, 192),
+    "w32_k4": ([9], 8320, 8128),
+    "w64_gate": (W64 * 8, 128, 576),
+    "w64_down": (W64 * 8, 1152, 64),
+    "w64_k2": (W64 * 2, 2304, 1984),
+    "w64_k2_small": (W64 * 8, 320, 192),
+    "w64_k4": ([33], 8320, 8128),
+    "w128": (W128 * 8, 1088, 1088),
+    "w128_gate": (W128 * 8, 512, 576),
+    "w128_down": (W128 * 8, 1088, 64),
+    "w128_narrow": (W128 * 8, 512, 256),
+    "w128_narrow_nt": (W128 * 8, 2112, 256),
+    "w160": (W160 * 8, 1088, 1088),
+    "w160_gate": (W160 * 8, 512, 576),
+    "w160_down": (W160 * 8, 1088, 64),
+    "w160_narrow_nt": (W160 * 8, 2112, 256),
+    # one GEMM on the streaming kernels, the other on the large-batch ones
+    "down_streams": ([150, 160, 161, 128, 129, 257, 100, 127] * 8, 128, 640),
+    "gate_streams": ([63, 64, 65, 1, 0, 96, 97, 33] * 8, 2304, 384),
 }
+# MXFP8 weights of 128 MB and more where the shapes above have less
+STREAM_MX = {
+    "mx_w32": (W32 * 8, 1152, 2304),
+    "mx_w32_k2": (W32 * 2, 3968, 2176),
+    "mx_w32_k4": ([9], 8448, 8064),
+    "mx_w64_k2": (W64 * 2, 3968, 2176),
+    "mx_w64_k4": ([33], 8448, 8064),
+    "mx_w128": (W128 * 8, 1152, 1920),
+    "mx_w128_narrow": (W128 * 8, 4224, 256),
+}
+# the kernels of (bf16 gate/up, bf16 down, MXFP8 gate/up, MXFP8 down) on 256 compute units: "weight
+# rows / 64, activation rows, k groups, stages, nt" or "0", a large-batch kernel
+STREAM_TILES = {
+    "decode_few": ("1 32 4 3 0", "1 32 4 3 0", "1 32 4 3 0", "1 32 4 3 0"),
+    "decode_k_groups": ("1 32 4 3 0", "1 32 4 3 0", "1 32 4 3 0", "1 32 4 3 0"),
+    "decode_many": ("2 64 1 3 1", "2 64 1 3 1", "2 64 1 3 1", "2 64 1 3 0"),
+    "mid64": ("2 64 1 3 1", "2 64 1 3 1", "2 64 1 3 1", "2 64 1 3 1"),
+    "mid64_few": ("1 64 2 4 0", "1 64 2 4 0", "1 64 2 4 0", "1 64 2 4 0"),
+    "mid64_wide": ("2 64 1 3 1", "2 64 1 3 1", "2 64 1 3 1", "2 64 1 3 1"),
+    "mid128": ("4 128 1 3 1", "2 128 1 4 1", "4 128 1 3 1", "2 128 1 4 1"),
+    "mid128_half": ("2 64 2 3 0", "2 128 1 4 0", "2 64 2 3 0", "2 128 1 4 0"),
+    "mid160": ("4 160 1 3 1", "2 160 1 4 1", "0", "4 128 1 3 0"),
+    "mid160_half": ("2 160 1 4 0", "2 160 1 4 0", "2 128 1 4 0", "2 128 1 4 0"),
+    "one_expert": ("1 64 2 4 0", "1 64 2 4 0", "1 64 2 4 0", "1 64 2 4 0"),
+    "w32": ("2 32 1 3 1", "2 32 1 3 1", "2 32 1 3 1", "2 32 1 3 0"),
+    "w32_gate": ("2 32 1 3 0", "1 32 4 3 0", "2 32 1 3 0", "1 32 4 3 0"),
+    "w32_down": ("1 32 4 3 0", "2 32 1 3 0", "1 32 4 3 0", "2 32 1 3 0"),
+    "w32_k2": ("2 32 2 3 1", "2 32 2 3 1", "2 32 2 3 1", "2 32 2 3 0"),
+    "w32_k2_small": ("2 32 2 3 0", "2 32 2 3 0", "2 32 2 3 0", "2 32 2 3 0"),
+    "w32_k4": ("1 32 4 3 1", "1 32 4 3 1", "2 32 2 3 1", "1 32 4 3 0"),
+    "w64_gate": ("2 64 1 3 0", "1 64 2 4 0", "2 64 1 3 0", "1 64 2 4 0"),
+    "w64_down": ("1 64 2 4 0", "2 64 1 3 0", "1 64 2 4 0", "2 64 1 3 0"),
+    "w64_k2": ("2 64 2 3 1", "2 64 2 3 1", "2 64 2 3 1", "2 64 2 3 0"),
+    "w64_k2_small": ("2 64 2 3 0", "2 64 2 3 0", "2 64 2 3 0", "2 64 2 3 0"),
+    "w64_k4": ("1 64 2 4 1", "1 64 2 4 1", "2 64 2 3 1", "1 64 2 4 0"),
+    "w128": ("4 128 1 3 1", "4 128 1 3 1", "4 128 1 3 1", "4 128 1 3 0"),
+    "w128_gate": ("4 128 1 3 0", "2 128 1 4 0", "4 128 1 3 0", "2 128 1 4 0"),
+    "w128_down": ("2 64 2 3 0", "4 128 1 3 0", "2 64 2 3 0", "4 128 1 3 0"),
+    "w128_narrow": ("2 128 1 4 0", "2 128 1 4 0", "2 128 1 4 0", "2 128 1 4 0"),
+    "w128_narrow_nt": ("2 128 1 4 1", "0", "2 128 1 4 0", "0"),
+    "w160": ("4 160 1 3 1", "4 160 1 3 1", "0", "0"),
+    "w160_gate": ("4 160 1 3 0", "2 160 1 4 0", "0", "4 128 1 3 0"),
+    "w160_down": ("2 64 2 3 0", "4 160 1 3 0", "2 128 1 4 0", "0"),
+    "w160_narrow_nt": ("2 160 1 4 1", "0", "4 128 1 3 0", "0"),
+    "down_streams": ("0", "2 64 2 3 0", "0", "2 64 2 3 0"),
+    "gate_streams": ("2 128 1 4 1", "0", "2 128 1 4 0", "0"),
+    "mx_w32": (None, None, "2 32 1 3 1", "2 32 1 3 1"),
+    "mx_w32_k2": (None, None, "2 32 1 3 1", "2 32 2 3 1"),
+    "mx_w32_k4": (None, None, "1 32 4 3 1", "1 32 4 3 0"),
+    "mx_w64_k2": (None, None, "2 64 1 3 1", "2 64 2 3 1"),
+    "mx_w64_k4": (None, None, "1 64 2 4 1", "1 64 2 4 0"),
+    "mx_w128": (None, None, "4 128 1 3 1", "4 128 1 3 1"),
+    "mx_w128_narrow": (None, None, "2 128 1 4 1", "0"),
+}
+
+
+def mx_dims(H, F):
+    return (H + 127) // 128 * 128, (F + 127) // 128 * 128
 
 
 @pytest.mark.parametrize("name", list(STREAM))
@@ -115,11 +201,10 @@ def check_bf16(name, c, H, F):
         assert ((y[lo:hi] - ref).abs() <= bound).all(), (e, hi - lo)
 
 
-@pytest.mark.parametrize("name", ["decode_few", "decode_k_groups", "decode_many", "mid64", "mid64_few", "mid128",
-                                  "mid128_half", "mid160_half", "one_expert"])
+@pytest.mark.parametrize("name", [n for n in STREAM | STREAM_MX if n not in ("mid64_wide", "mid160")])
 def test_mxfp8_stream(name):
-    c, H, F = STREAM[name]
-    check_mxfp8(name, c, (H + 127) // 128 * 128, (F + 127) // 128 * 128)
+    c, H, F = (STREAM | STREAM_MX)[name]
+    check_mxfp8(name, c, *mx_dims(H, F))
 
 
 # Groups on the edges of the large-batch kernels' m-tiles (256 and 320 rows).  On a device's

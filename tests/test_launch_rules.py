@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_group_sizes import STREAM, STREAM_MX, STREAM_TILES, mx_dims
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2606_21712_amd", "csrc")
 
@@ -68,6 +70,30 @@ def test_tile_grid(rules):
 def stream_choices(rules, c, H, F, fp8):
     E, R = len(c), sum(c)
     return rules([f"stream {R} {E} {H} {F} 1 {fp8} 256", f"stream {R} {E} {F} {H} 0 {fp8} 256"])
+
+
+def test_stream_cases_reach_their_kernels(rules):
+    """The cases that the GPU tests run the streaming kernels on launch what their table says,
+    and together every tile in both GEMMs and data types: bf16 with both cache policies."""
+    seen = set()
+    for name, tiles in STREAM_TILES.items():
+        c, H, F = (STREAM | STREAM_MX)[name]
+        for fp8 in (0, 1):
+            want = list(tiles[2 * fp8:2 * fp8 + 2])
+            if want == [None, None]:
+                continue
+            got = stream_choices(rules, c, *(mx_dims(H, F) if fp8 else (H, F)), fp8)
+            assert got == want, (name, fp8)
+            seen |= {(fp8, g, t) for g, t in enumerate(got)}
+    assert set(STREAM_TILES) == set(STREAM | STREAM_MX)
+    both = ["4 128 1 3", "2 128 1 4", "2 64 1 3", "2 64 2 3", "1 64 2 4", "2 32 1 3", "2 32 2 3", "1 32 4 3"]
+    for g in (0, 1):
+        for t in both + ["4 160 1 3", "2 160 1 4"]:
+            assert {(0, g, t + " 0"), (0, g, t + " 1")} <= seen, (g, t)
+        for t in both:
+            assert {(1, g, t + " 0"), (1, g, t + " 1")} & seen, (g, t)
+            if g == 0 or not t.startswith("1 "):       # (MXFP8 down on 64 weight rows: only small weights)
+                assert (1, g, t + " 1") in seen, (g, t)
 
 
 # (mean rows, H, F, experts, MXFP8, GEMM, streams): both sides of the lines, where they were measured
