@@ -77,16 +77,15 @@ def tail_plan(n: int, G: int, KT: int):
 
 
 def mtiles(counts, extra: int) -> np.ndarray:
-    """m-tiles per expert: 256-row tiles, the last taking up to 256 + extra rows."""
+    """m-tiles per expert, of up to 256 + extra rows."""
     c = np.asarray(counts, dtype=np.int64)
-    rest = np.maximum(c - extra, 0)
-    return np.where(c == 0, 0, np.maximum(1, (rest + 255) // 256))
+    return (c + 255 + extra) // (256 + extra)
 
 
 def down_tiles(offsets: np.ndarray, H: int, extra: int) -> tuple[int, int]:
     """(actual, upper bound) of the down projection's output tiles (256 columns;
-    extra = 64 for the bf16 GEMMs, whose last m-tile of an expert takes up to 320
-    rows, 0 for the MXFP8 ones)."""
+    extra = 64 for the bf16 GEMMs, whose m-tiles hold up to 320 rows, 0 for the MXFP8
+    ones)."""
     counts = np.diff(np.asarray(offsets, dtype=np.int64))
     nt = (H + 255) // 256
     actual = int(mtiles(counts, extra).sum()) * nt

@@ -2,7 +2,8 @@
 of the eager step on the same inputs -- replays interleaved with eager steps on the
 same layer buffers, and replays after new inputs are copied into the captured
 tensors (the graph reads them by address).  bf16 with and without the gather, with
-a shared expert, and the MXFP8 layer."""
+a shared expert, and the MXFP8 layer; each on the streaming GEMMs that its sizes choose and,
+under a compute-unit budget, on the large-batch ones (tile prefix, queues, tail reduction)."""
 import pytest
 import torch
 
@@ -26,7 +27,16 @@ def _weights(I, mx):
 
 
 @pytest.mark.parametrize("mode", ["bf16_gather", "bf16_xperm", "mxfp8"])
-def test_layer_graph_replays_match_eager(mode):
+@pytest.mark.parametrize("budget", [0, 256])
+def test_layer_graph_replays_match_eager(mode, budget):
+    moe.set_cu_budget(budget)
+    try:
+        check_replays(mode)
+    finally:
+        moe.set_cu_budget(0)
+
+
+def check_replays(mode):
     c = CFG
     Ia, Ib = moegen.make_inputs(c), moegen.make_inputs(c, seed=c.seed + 1)
     mx = mode == "mxfp8"

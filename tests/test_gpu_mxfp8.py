@@ -209,8 +209,18 @@ def run_mxfp8_layer(c, I, gather=True):
     return layer, wq
 
 
-@pytest.mark.parametrize("name", list(CASES))
-def test_layer_mxfp8(name):
+@pytest.mark.parametrize("name,budget", [(n, b) for n in CASES for b in (0, 256)])
+def test_layer_mxfp8(name, budget):
+    """On the kernels that the sizes choose (small groups: streaming) and, under a budget of as
+    many compute units as the device has, on the large-batch ones."""
+    moe.set_cu_budget(budget)
+    try:
+        check_layer(name)
+    finally:
+        moe.set_cu_budget(0)
+
+
+def check_layer(name):
     """Unique results bit-exact (routing, grouping, x and weight codes); h checked as a
     valid quantization of the exact h within the accumulation bound; y_perm against the
     fp64 product of the kernel's own h with the quantized W_down (accumulation bound

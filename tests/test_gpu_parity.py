@@ -99,8 +99,21 @@ RANDOM_CASES = _random_cases()
 CASES.update(RANDOM_CASES)
 
 
-@pytest.mark.parametrize("name", list(CASES))
-def test_layer_parity(name):
+# On the device's own compute units shapes this small take the streaming kernels; a budget of as
+# many as the device has leaves them to the large-batch ones.
+LARGE_KERNELS = ["mixtral_small", "zipf_small", "deepseek_small", "memc_small", "longk_small"]
+
+
+@pytest.mark.parametrize("name,budget", [(n, 0) for n in CASES] + [(n, 256) for n in LARGE_KERNELS])
+def test_layer_parity(name, budget):
+    moe.set_cu_budget(budget)
+    try:
+        check_layer(name)
+    finally:
+        moe.set_cu_budget(0)
+
+
+def check_layer(name):
     I = inputs(name)
     c = I.cfg
     # the random shapes alternate between the grouped-copy and the gather path
@@ -131,9 +144,8 @@ def test_layer_parity(name):
     assert err <= tol
 
 
-# Group sizes around the m-tile edges: an expert's last m-tile holds up to 320 rows
-# (256 + 64), so 257..320 rows make one tile, 321 two, 576 two (256 + 320), 577
-# three; plus 1, 64, 65 and an empty expert.
+# Group sizes around the m-tile edges of the large-batch kernels: bf16 tiles hold up to 320
+# rows (320 rows make one, 321 and 640 two), MXFP8 ones 256; plus 1, 64, 65 and an empty expert.
 EDGE_COUNTS = [256, 257, 300, 320, 321, 512, 576, 577, 1, 64, 65, 0]
 
 
@@ -151,17 +163,23 @@ def edge_count_inputs(H=256, F=320, seed=22):
     return I, expert
 
 
-def test_last_m_tile_extra_rows():
-    """Groups whose sizes sit on the m-tile edges (including the 320-row last tile)
-    against the oracle, through the copy and the gather paths (bitwise equal)."""
+@pytest.mark.parametrize("budget", [0, 256, 4])
+def test_last_m_tile_extra_rows(budget):
+    """Groups whose sizes sit on the m-tile edges against the oracle, through the copy and
+    the gather paths (bitwise equal): on the streaming kernels' tiles, and under budgets on
+    the large-batch kernels' (320 rows), each on a compute unit of its own and several in turn."""
     I, expert = edge_count_inputs()
     c = I.cfg
-    log(f"[gpu] edge group sizes {EDGE_COUNTS}: T={c.T} H={c.H} F={c.F}")
+    log(f"[gpu] edge group sizes {EDGE_COUNTS}: T={c.T} H={c.H} F={c.F} budget={budget}")
     o = oracle_layer(I)
     assert np.array_equal(o["counts"], np.array(EDGE_COUNTS))
     assert np.array_equal(o["ids"][:, 0], expert)
-    g = run_layer(I)
-    b = run_layer(I, gather=True)
+    moe.set_cu_budget(budget)
+    try:
+        g = run_layer(I)
+        b = run_layer(I, gather=True)
+    finally:
+        moe.set_cu_budget(0)
     assert np.array_equal(g["ids"], o["ids"])
     assert np.array_equal(g["offsets"], o["offsets"])
     yp = f64(g["y_perm"])
