@@ -498,7 +498,7 @@ def route_probe(reps: int = 10):
 PEAK_FP8_TFLOPS = 5000.0        # MI355X dense fp8 MFMA
 
 
-def mxfp8_bench(config: str, steps: int, warmup: int, profile_run: bool = False):
+def mxfp8_bench(c, steps: int, warmup: int, profile_run: bool = False):
     """The layer with MXFP8 expert GEMMs on one workload: one JSON line (a separate
     measurement; the bf16 line is the headline).  Weights are quantized once, outside
     the timed region; inside it every step routes, permutes, quantizes x, runs both
@@ -507,7 +507,6 @@ def mxfp8_bench(config: str, steps: int, warmup: int, profile_run: bool = False)
 
     import moegen
     import paper_2606_21712_amd as moe
-    c = moegen.CONFIGS[config]
     log(f"mxfp8: generating {c.name}")
     I = moegen.make_inputs(c)
     x, logits = to_dev(I.x, torch), to_dev(I.logits, torch)
@@ -918,8 +917,10 @@ def kernel_label(name: str) -> str:
     if not m:
         return name.split("(")[0].strip()
     base, tmpl = m.group(1), m.group(2) or ""
-    if base == "grouped_gemm_bf16" or base == "grouped_gemm_f32" or base == "grouped_gemm_fp8":
+    if base in ("grouped_gemm_bf16", "grouped_gemm_f32", "grouped_gemm_f32_small", "grouped_gemm_fp8"):
         return "gemm1" if tmpl.startswith("<true") else "gemm2"
+    if base == "stream_gemm":                            # <MXFP8, gate/up, tile ...>
+        return "gemm1" if tmpl.split(",")[1].strip() == "true" else "gemm2"
     return base
 
 
@@ -1208,7 +1209,7 @@ def summarize(root, c, warmup: int, steps: int, gather: bool = True, mx: bool = 
                 lines.append(f"| {lab} | {100 * m['TCC_HIT'] / tot:.1f} | {past} | {lat} |" if tot else
                              f"| {lab} | - | {past} | {lat} |")
             lines.append("")
-        g = per.get("gemm1")
+        g = per.get("gemm1") if "@" not in c.name else None      # (another batch: maybe other kernels)
         if g and "FETCH_SIZE" in g and "WRITE_SIZE" in g and factor:
             hbm = float(np.mean(g["FETCH_SIZE"])) * 1024 * factor["FETCH_SIZE"] + \
                 float(np.mean(g["WRITE_SIZE"])) * 1024 * factor["WRITE_SIZE"]
@@ -1318,6 +1319,13 @@ def summarize_dense(root):
     print("\n".join(lines))
 
 
+def workload(name: str, tokens: int = 0):
+    """A named workload, or its layer on another number of tokens (named name@tokens)."""
+    import moegen
+    c = moegen.CONFIGS[name]
+    return c.scaled(name=f"{name}@{tokens}", T=tokens) if tokens else c
+
+
 def main():
     import moegen
 
@@ -1326,6 +1334,8 @@ def main():
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--config", default="memconstrained", choices=sorted(moegen.CONFIGS))
+    ap.add_argument("--tokens", type=int, default=0,
+                    help="the workload's layer on this many tokens instead (decode and short batches)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-gather", action="store_true",
                     help="materialize x_perm in moe_permute instead of gathering rows in the grouped FFN")
@@ -1364,7 +1374,7 @@ def main():
     if args.summarize and args.dense:
         return summarize_dense(args.summarize)
     if args.summarize:
-        return summarize(args.summarize, moegen.CONFIGS[args.config], args.warmup, args.steps,
+        return summarize(args.summarize, workload(args.config, args.tokens), args.warmup, args.steps,
                          gather=not args.no_gather, mx=args.mxfp8)
     if args.copy_calibration:
         return copy_calibration(args.copy_calibration)
@@ -1381,7 +1391,7 @@ def main():
     if args.router_probe:
         return router_probe()
     if args.mxfp8:
-        return mxfp8_bench(args.config, args.steps, args.warmup, profile_run=args.profile_run)
+        return mxfp8_bench(workload(args.config, args.tokens), args.steps, args.warmup, profile_run=args.profile_run)
     if args.sweep:
         return expert_batch_sweep(args.sweep, args.steps, args.warmup)
 
@@ -1400,7 +1410,7 @@ def main():
         sys.exit(1)
     moe.lib()                                        # fail loudly if the library is missing
 
-    cfg = moegen.CONFIGS[args.config]
+    cfg = workload(args.config, args.tokens)
     c = cfg
     t0 = time.perf_counter()
     log(f"generating inputs for {c.name}: T={c.T} H={c.H} E={c.E} k={c.k} F={c.F} Fs={c.Fs} {c.dtype}")

@@ -31,6 +31,17 @@ def test_kernel_labels():
                "(moe::(anonymous namespace)::GemmArgs)") == "gemm2"
     assert lab("void moe::(anonymous namespace)::grouped_gemm_fp8_kernel<true, true>"
                "(moe::(anonymous namespace)::GemmArgsF8)") == "gemm1"
+    # the kernels for small groups: MXFP8 first, then gate/up; fp32 on 32 x 32 tiles
+    for mx in ("false", "true"):
+        for swiglu, want in (("true", "gemm1"), ("false", "gemm2")):
+            assert lab(f"void moe::(anonymous namespace)::stream_gemm_kernel<{mx}, {swiglu}, 2, 32, 1, 3, true>"
+                       "(moe::(anonymous namespace)::StreamArgs)") == want
+    assert lab("void moe::(anonymous namespace)::grouped_gemm_f32_small_kernel<true>"
+               "(moe::(anonymous namespace)::GemmArgsF)") == "gemm1"
+    assert lab("void moe::(anonymous namespace)::grouped_gemm_f32_kernel<false>"
+               "(moe::(anonymous namespace)::GemmArgsF)") == "gemm2"
+    assert lab("void moe::(anonymous namespace)::permute_small_kernel<4>(int const*, long, int, int, int, int*, int*, "
+               "int*, int*)") == "permute_small"
     assert lab("void moe::(anonymous namespace)::combine_kernel<true, 4, 8>(unsigned char const*, int const*, "
                "float const*, unsigned char const*, long, int, long, int, unsigned char*)") == "combine"
     assert lab("void moe::(anonymous namespace)::route_kernel<8, 8, true, 4>(float const*, long, int, int, int, "
@@ -39,6 +50,13 @@ def test_kernel_labels():
                "int const*, int*, int*, int*, int*)") == "permute_rank"
     assert lab("moe::(anonymous namespace)::tile_prefix_kernel(int const*, int, int, int, int*, int*)") == \
         "tile_prefix"
+
+
+def test_workload_tokens():
+    assert bench.workload("mixtral4k") is moegen.CONFIGS["mixtral4k"]
+    c = bench.workload("mixtral4k", 24)
+    assert (c.T, c.R, c.H, c.F, c.E, c.k) == (24, 48, 4096, 14336, 8, 2)
+    assert bench.measured_traffic(c.name) is None          # no other batch's counters
 
 
 def test_algorithmic_work():
