@@ -61,10 +61,21 @@ struct StreamArgs {
 // 16-byte chunk c of row r sits at chunk c ^ ((r >> 1) & 7): conflict-free operand reads.
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
+// LDS of a workgroup (the kernel's stages), and the wavefronts per SIMD that it leaves room for:
+// what the register allocation is bounded by.
+constexpr int stream_stage(bool fp8, int wn, int mr) {
+  return (64 * wn + mr) * kRowBytes + (fp8 ? (64 * wn + (mr + 63) / 64 * 64) * 4 : 0);
+}
+constexpr int stream_waves(bool fp8, int wn, int mr, int kg, int s) {
+  const int fit = 160 * 1024 / (s * kg * stream_stage(fp8, wn, mr) + (s == 3 ? 16 : 0));
+  const int waves = fit * 2 * wn * kg / 4;
+  return waves < 2 ? waves : 2;
+}
+
 // 2 x WN wavefronts: each MR / 2 activation rows x 64 weight rows of the tile (GEMM-1: 32
 // gate and 32 up rows of the same features).  MR: activation rows per tile; S: stages.
 template <bool FP8, bool SWIGLU, int WN, int MR, int KG, int S, bool NTW>
-__global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArgs p) {
+__global__ __launch_bounds__(128 * WN * KG, stream_waves(FP8, WN, MR, KG, S)) void stream_gemm_kernel(StreamArgs p) {
   constexpr int kElt = FP8 ? 1 : 2;
   constexpr int kBN = 64 * WN;                       // weight rows of the tile
   constexpr int kCols = SWIGLU ? kBN / 2 : kBN;      // output columns of the tile
@@ -76,7 +87,8 @@ __global__ __launch_bounds__(128 * WN * KG, 2) void stream_gemm_kernel(StreamArg
   constexpr int kWSOff = kAOff + MR * kRowBytes;     // MXFP8 scale dwords: weight rows, then activation rows
   constexpr int kASOff = kWSOff + kBN * 4;
   constexpr int kARows64 = (MR + 63) / 64 * 64;
-  constexpr int kStage = FP8 ? kASOff + kARows64 * 4 : kWSOff;
+  constexpr int kStage = stream_stage(FP8, WN, MR);
+  static_assert(kStage == (FP8 ? kASOff + kARows64 * 4 : kWSOff), "stage layout");
   constexpr int kBlocks = MR / 32;                   // 32-row blocks of the tile: block 2 mi + wm is
   constexpr int NB = (kBlocks + 1) / 2;              // the mi-th of wavefront row wm
   static_assert(S == 3 || S == 4, "stages");
