@@ -5,17 +5,19 @@
 // of the same features so that silu(g) * u is formed in registers.  Products and sums
 // are fp32 (v_mfma_f32_32x32x2_f32); silu uses the full-precision expf and division.
 //
-// What bounds it: the fp32 matrix rate (256 flop per cycle and compute unit, an eighth
-// of a bf16 step's rate for the same bytes), so a plain two-stage pipeline is enough, and
-// what is left is evenness: tiles of 64 rows x 64 weight rows x 32 k per step, four
-// wavefronts of 32 x 32, 16 KB per stage, four workgroups per compute unit, whose MFMAs
-// run through each other's barriers.  One launch covers every expert's tiles: the grid
-// holds the host's bound on them, and the workgroups past the device's count leave.
+// What bounds it: the fp32 matrix rate (256 flop per cycle and compute unit, an eighth of
+// a bf16 step's rate for the same bytes), and short of that evenness.  Tiles of 64 rows x
+// 64 weight rows x 32 k per step, four wavefronts of 32 x 32, two stages of 16 KB, four
+// workgroups per compute unit, whose MFMAs run through each other's waits and barriers while
+// all four are there.  One launch covers every expert's tiles: the grid holds the host's
+// bound on them, and the workgroups past the device's count leave.
 // Measured against 64 x 64 tiles of vector FMAs staged through registers: 2000 tokens,
-// H 1024, 8 experts, top-2, F 2048: GEMM-1 477 -> 338 us (99 TFLOP/s), GEMM-2 305 -> 196 us;
-// 256 tokens, H 256, F 512: 37 -> 11 us and 35 -> 14 us.  The library's dense fp32 matmul
-// reaches 151 TFLOP/s at 8192^3.  With 64 x 128 tiles (three workgroups per compute unit)
-// some compute units held three of the 512 down-projection tiles and some one: 232 us.
+// H 1024, 8 experts, top-2, F 2048: GEMM-1 477 -> 338 us (99 TFLOP/s), GEMM-2 305 -> 196 us
+// (86); 256 tokens, H 256, F 512: 37 -> 9.8 us and 35 -> 6.5 us (on the small kernel below).
+// The library's dense fp32 matmul reaches 151 TFLOP/s at 8192^3.  At 2000 tokens the down
+// projection has 1040 to 1088 tiles for 1024 places, gate/up 4160 to 4352: the 16 to 64 over
+// a whole round run alone at the end, with every wait exposed.  With 64 x 128 tiles (three
+// workgroups per compute unit) some compute units held three of its 512 and some one: 232 us.
 #include "group_locate.h"
 #include "lds_stage.h"
 #include "moe_internal.h"
@@ -157,9 +159,11 @@ __global__ __launch_bounds__(kFThreads, 4) void grouped_gemm_f32_kernel(GemmArgs
 
 // Small layers, whose tiles of 64 x 64 leave compute units idle.  The chain of k steps of one
 // tile bounds them, so the tile is 32 rows x 32 weight rows (GEMM-1: 16 gate + 16 up) and
-// its four wavefronts split k, 32 at a time in turn: a quarter of the steps.  Each streams
+// its four wavefronts split k, 32 at a time in turn: a quarter of the steps.  Each takes
 // its own part of both operands through two LDS stages of its own, without a barrier, and
-// the four sums meet in LDS at the end, added in wavefront order.  Measured, 64 x 64 ->
+// the four sums meet in LDS at the end, added in wavefront order.  A step asks to wait for its
+// own stage only; the compiler does not tell the refill of a stage just read from the other's
+// loads and waits for all of them at every second step.  Measured, 64 x 64 ->
 // this: 512 rows over 8 experts, F 512, H 256, down 14.3 -> 9.0 us; 2 rows, H 4096,
 // F 1024, gate/up 74 -> 28 us, down 22 -> 11 us.
 template <bool SWIGLU>
