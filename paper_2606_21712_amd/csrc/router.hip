@@ -40,6 +40,63 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v + __uint_as_float(dpp<0x4E>(__float_as_uint(v)));
 }
 
+// The gate of moe_route on one token's E logits, held by four lanes (g = lane % 4) as experts
+// g V .. g V + V - 1 (key: orderable, 0 past E): the k largest, ties to the lower expert id,
+// softmax over the selected (renormalize) or all logits.  Lane g = 0 of a valid token writes.
+template <int V, int KMAX>
+__device__ __forceinline__ void select_topk(const float (&vals)[V], uint32_t (&key)[V], int e0, int g, int E, int k,
+                                            int renormalize, bool valid, int64_t t, int32_t* __restrict__ topk_ids,
+                                            float* __restrict__ topk_w) {
+  uint32_t selk[KMAX];
+  uint32_t sele[KMAX];
+#pragma unroll
+  for (int j = 0; j < KMAX; ++j) {
+    if (j < k) {
+      uint32_t m = key[0];
+#pragma unroll
+      for (int v = 1; v < V; ++v) m = max(m, key[v]);
+      m = quad_max(m);
+      uint32_t id = 0xFFFFFFFFu;
+#pragma unroll
+      for (int v = V - 1; v >= 0; --v) id = key[v] == m ? uint32_t(e0 + v) : id;
+      id = quad_min(id);
+#pragma unroll
+      for (int v = 0; v < V; ++v) key[v] = uint32_t(e0 + v) == id ? 0u : key[v];
+      selk[j] = m;
+      sele[j] = id;
+    } else {
+      selk[j] = 0u;
+      sele[j] = 0u;
+    }
+  }
+  const float lmax = from_orderable(selk[0]);
+  float p[KMAX];
+  float denom = 0.f;
+#pragma unroll
+  for (int j = 0; j < KMAX; ++j) {
+    if (j < k) {
+      p[j] = expf(from_orderable(selk[j]) - lmax);
+      denom += p[j];
+    }
+  }
+  if (!renormalize) {
+    float sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (e0 + v < E) sum += expf(vals[v] - lmax);
+    denom = quad_sum(sum);
+  }
+  if (valid && g == 0) {
+#pragma unroll
+    for (int j = 0; j < KMAX; ++j) {
+      if (j < k) {
+        topk_ids[t * k + j] = int32_t(sele[j]);
+        topk_w[t * k + j] = p[j] / denom;
+      }
+    }
+  }
+}
+
 // Larger batches: WV (two or four) wavefronts per block, 16 tokens each.  Memory bounds it: x is
 // read once, the router matrix once per block, from L2.  Token rows and router rows go
 // through a ring of four LDS stages of 64 k each, by direct global -> LDS loads of whole
@@ -223,54 +280,7 @@ __global__ __launch_bounds__(WV * 64) void router_lds_kernel(const uint16_t* __r
     for (int v = 0; v < V; ++v)
       if (e0 + v < E) logits_out[t * E + e0 + v] = vals[v];
   }
-  uint32_t selk[KMAX];
-  uint32_t sele[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j < k) {
-      uint32_t m = key[0];
-#pragma unroll
-      for (int v = 1; v < V; ++v) m = max(m, key[v]);
-      m = quad_max(m);
-      uint32_t id = 0xFFFFFFFFu;
-#pragma unroll
-      for (int v = V - 1; v >= 0; --v) id = key[v] == m ? uint32_t(e0 + v) : id;
-      id = quad_min(id);
-#pragma unroll
-      for (int v = 0; v < V; ++v) key[v] = uint32_t(e0 + v) == id ? 0u : key[v];
-      selk[j] = m;
-      sele[j] = id;
-    } else {
-      selk[j] = 0u;
-      sele[j] = 0u;
-    }
-  }
-  const float lmax = from_orderable(selk[0]);
-  float p[KMAX];
-  float denom = 0.f;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j < k) {
-      p[j] = expf(from_orderable(selk[j]) - lmax);
-      denom += p[j];
-    }
-  }
-  if (!renormalize) {
-    float sum = 0.f;
-#pragma unroll
-    for (int v = 0; v < V; ++v)
-      if (e0 + v < E) sum += expf(vals[v] - lmax);
-    denom = quad_sum(sum);
-  }
-  if (valid && g == 0) {
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-      if (j < k) {
-        topk_ids[t * k + j] = int32_t(sele[j]);
-        topk_w[t * k + j] = p[j] / denom;
-      }
-    }
-  }
+  select_topk<V, KMAX>(vals, key, e0, g, E, k, renormalize, valid, t, topk_ids, topk_w);
 }
 
 // Small batches: four wavefronts per 16 tokens, each a quarter of the k range, their fp32
@@ -423,54 +433,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_splitk_kernel(const u
     for (int v = 0; v < V; ++v)
       if (e0 + v < E) logits_out[t * E + e0 + v] = vals[v];
   }
-  uint32_t selk[KMAX];
-  uint32_t sele[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j < k) {
-      uint32_t m = key[0];
-#pragma unroll
-      for (int v = 1; v < V; ++v) m = max(m, key[v]);
-      m = quad_max(m);
-      uint32_t id = 0xFFFFFFFFu;
-#pragma unroll
-      for (int v = V - 1; v >= 0; --v) id = key[v] == m ? uint32_t(e0 + v) : id;
-      id = quad_min(id);
-#pragma unroll
-      for (int v = 0; v < V; ++v) key[v] = uint32_t(e0 + v) == id ? 0u : key[v];
-      selk[j] = m;
-      sele[j] = id;
-    } else {
-      selk[j] = 0u;
-      sele[j] = 0u;
-    }
-  }
-  const float lmax = from_orderable(selk[0]);
-  float p[KMAX];
-  float denom = 0.f;
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) {
-    if (j < k) {
-      p[j] = expf(from_orderable(selk[j]) - lmax);
-      denom += p[j];
-    }
-  }
-  if (!renormalize) {
-    float sum = 0.f;
-#pragma unroll
-    for (int v = 0; v < V; ++v)
-      if (e0 + v < E) sum += expf(vals[v] - lmax);
-    denom = quad_sum(sum);
-  }
-  if (valid && g == 0) {
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-      if (j < k) {
-        topk_ids[t * k + j] = int32_t(sele[j]);
-        topk_w[t * k + j] = p[j] / denom;
-      }
-    }
-  }
+  select_topk<V, KMAX>(vals, key, e0, g, E, k, renormalize, valid, t, topk_ids, topk_w);
 }
 
 template <int NB>
